@@ -67,13 +67,14 @@ enum {
  * one pixel per thread, backward shape = forward shape.  The supported (tile, batch,
  * pixels per thread) launch shapes are (8,64,1) (8,128,1) (16,128,1) (16,256,1) (16,64,2)
  * (16,128,2) (16,256,2) (16,64,4) (32,256,4) (32,512,2); others give AGS_ERR_NOT_SUPPORTED at
- * launch. */
+ * launch.  Of a shape the tile size selects a kernel; how many list entries and pixels a lane
+ * takes follows from the number of tiles in the launch. */
 typedef struct ags_config {
     float alpha_min, alpha_max, t_min, blur, z_near, fov_clamp;
     float bg[3];
     int tile;          /* tile edge in pixels: 8, 16 or 32 (binning and raster) */
-    int batch;         /* forward: Gaussians staged in LDS per batch: 64, 128, 256 or 512 */
-    int px_per_thread; /* forward: pixels per thread: 1, 2 or 4 */
+    int batch;         /* forward launch shape: 64, 128, 256 or 512 */
+    int px_per_thread; /* forward launch shape: 1, 2 or 4 */
     int batch_bwd;     /* backward launch shape; 0 = same as the forward */
     int px_per_thread_bwd;
 } ags_config;

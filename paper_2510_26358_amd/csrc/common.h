@@ -10,9 +10,12 @@ namespace ags {
 
 constexpr int kMaxViews = AGS_MAX_VIEWS;
 constexpr int kRecFloats = 12;       // projected record: u v a b c o z ex ey r g b
-// per-pair 2D adjoint: 5 pixel moments of dL/dpower (turned into the centre and conic
-// adjoints by the projection backward), then o, r, g, b, z
+// per-pair 2D adjoint: 5 pixel moments of p = dL/dpower (turned into the centre and conic
+// adjoints by the projection backward), the sum of p (o dL/do), then r, g, b, z.  The kGrad2dSplit
+// sums of p, whose terms cancel, are kept in two parts (slots 0..5 and 10..15) that different waves
+// add to: half as long a chain of float additions into each.
 constexpr int kGrad2d = 10;
+constexpr int kGrad2dSplit = 6;
 constexpr int kGrad2dStride = 16;  // 64-byte rows: a row is one cache line
 
 // Static per-batch table passed by value to kernels (kernel arguments).
@@ -336,54 +339,66 @@ __device__ __forceinline__ float wave_transpose_sum16(const float (&v)[16]) {
     return w1;
 }
 
-// Sum of 10 per-lane values over the wave with the same butterfly, the values placed in
-// slots {0, 1, 2, 4, 5} (v < 5) and {8, 9, 10, 12, 13} (v >= 5) so that no stage pairs two
-// empty slots: 5 + 3 lane swaps, then 3 DPP stages.  Lanes of empty slots end with
-// meaningless sums (only empty-slot data flows into them).  On return lane L holds the
-// total of slot (L >> 2) & 15.
-__device__ __forceinline__ float wave_transpose_sum10(const float (&v)[10]) {
-    const int lane = __lane_id();
-    // stage 1 (lane bit 5): value j and j + 5 share slot low bits kSlot[j] = {0, 1, 2, 4, 5}
-    float w8[5];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 5]), false,
-                                                  false);
-        w8[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+// The ten per-Gaussian sums of a wave whose lane l covers column x = l % 8 of an 8-wide block.
+// dx depends on the column alone, so the seven values h, h dy, h dy^2 and c[0..3] are summed over
+// the columns' lanes first (lane bits 3, 5, 4, a transposing butterfly: each lane ends with one of
+// them for its column), and dx and dx^2 are applied there, before the sum over the eight columns.
+// Bits 3 and 2 use DPP adds whose bank mask writes half of the lanes (8 cycles a pair of values,
+// where a lane swap and an add take 10 and two selects and a DPP add 12).  Returned: the total of
+// value column_sum_of(lane) on ten lanes, other lanes hold nothing of use.
+__device__ __forceinline__ float wave_column_sums(float h, float hy, float hyy, const float (&c)[4], float dx) {
+    float r0, r1, r2, r3;
+    // two wait states before a DPP or lane-swap read of a vector result (the compiler inserts them
+    // around its own instructions, not around these)
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "s_nop 1"
+        : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+        : "v"(h), "v"(hy), "v"(hyy), "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
+    auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(r0), __float_as_uint(r1), false, false);
+    const float p0 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    p = __builtin_amdgcn_permlane32_swap(__float_as_uint(r2), __float_as_uint(r3), false, false);
+    const float p1 = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    p = __builtin_amdgcn_permlane16_swap(__float_as_uint(p0), __float_as_uint(p1), false, false);
+    const float z = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const float zx = z * dx, zxx = zx * dx;
+    float s, t;
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %1, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 1"
+        : "=&v"(s), "=&v"(t)
+        : "v"(z), "v"(zx), "v"(zxx));
+    s += dpp_mov<0xB1>(s);  // quad_perm [1, 0, 3, 2]: lane ^ 1
+    t += dpp_mov<0xB1>(t);
+    s += dpp_mov<0x4E>(s);  // quad_perm [2, 3, 0, 1]: lane ^ 2
+    t += dpp_mov<0x4E>(t);
+    return __lane_id() == 1 ? t : s;
+}
+
+// Which of the ten sums wave_column_sums leaves on a lane, in the order h dx, h dy, h dx^2, h dx dy,
+// h dy^2, h, c[0..3]; -1 for none.
+__device__ __forceinline__ int column_sum_of(int lane) {
+    switch (lane) {
+        case 4: return 0;
+        case 8: return 1;
+        case 1: return 2;
+        case 12: return 3;
+        case 32: return 4;
+        case 0: return 5;
+        case 40: return 6;
+        case 16: return 7;
+        case 24: return 8;
+        case 48: return 9;
+        default: return -1;
     }
-    // stage 2 (lane bit 4): slot low bits (0, 4) -> w8[0], w8[3]; (1, 5) -> w8[1], w8[4];
-    // (2, 6) -> w8[2] and an empty slot
-    float w4[3];
-    {
-        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w8[0]), __float_as_uint(w8[3]), false, false);
-        w4[0] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w8[1]), __float_as_uint(w8[4]), false, false);
-        w4[1] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w8[2]), __float_as_uint(w8[2]), false, false);
-        w4[2] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    // stage 3 (lane bit 3): (w4[0], w4[2]); w4[1]'s partner slot is empty, so both lane
-    // halves simply add their neighbour's w4[1]
-    float w2[2];
-    {
-        const bool hi = lane & 8;
-        const float send = hi ? w4[0] : w4[2];
-        const float keep = hi ? w4[2] : w4[0];
-        w2[0] = keep + dpp_mov<0x128>(send);  // row_ror:8 == lane ^ 8 inside a row
-        w2[1] = w4[1] + dpp_mov<0x128>(w4[1]);
-    }
-    // stage 4 (lane bit 2), then lane bits 0 and 1
-    float w1;
-    {
-        const bool hi = lane & 4;
-        const float send = hi ? w2[0] : w2[1];
-        const float keep = hi ? w2[1] : w2[0];
-        w1 = keep + dpp_mov<0x141>(send);  // row_half_mirror: lane i <-> 7 - i in 8-lane halves
-    }
-    w1 += dpp_mov<0xB1>(w1);  // quad_perm [1, 0, 3, 2]: lane ^ 1
-    w1 += dpp_mov<0x4E>(w1);  // quad_perm [2, 3, 0, 1]: lane ^ 2
-    asm volatile("" : "+v"(w1));  // the last step stays one DPP add, ahead of the caller's branch
-    return w1;
 }
 
 // Host-side launchers (one per kernel family), defined next to their kernels.
@@ -496,8 +511,9 @@ struct RasterArgs {
     // zeroed per pixel (or null): the backward's dense depth and second-moment adjoints
     float* zero_px[2];
 };
-// The (tile, pixels per thread, LDS batch) launch shapes compiled for both raster kernels:
-// writes up to n_max of them and returns how many there are.
+// The (tile, pixels per thread, LDS batch) shapes that a configuration may name (the raster kernels
+// take their blocks by the number of tiles, not by the last two): writes up to n_max of them and
+// returns how many there are.
 int raster_shapes(int* tile, int* ppt, int* batch, int n_max);
 int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_t s);
 
@@ -524,7 +540,7 @@ struct RasterBwdArgs {
     const uint8_t* mask;
     float l1_scale[kMaxViews];   // (1 - lambda_ssim) w_l1 / (3 n_b)
     float* loss_partials;        // one per block (loss mode)
-    float* grad2d;               // [n_pairs][16] (ten used); rows of visible pairs cleared
+    float* grad2d;               // [n_pairs][kGrad2dStride]; rows of visible pairs cleared
 };
 int launch_raster_bwd(const RasterBwdArgs& a, int T, int batch, int ppt, hipStream_t s);
 // The backward's clears in one launch, for a backward whose forward did not leave them done

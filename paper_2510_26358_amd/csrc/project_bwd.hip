@@ -80,10 +80,10 @@ __device__ __forceinline__ void geometry_bwd(const ProjectBwdArgs& a) {
         for (int k = 0; k < 16; ++k) pose[k] = 0.f;
         if (vis) {
             const float* g2 = opaque_ptr(a.grad2d) + q * kGrad2dStride;
-            // slots 0..4 hold pixel moments of dL/dpower = o h (h = dL/do per pixel) without
-            // the factor o: sum h dx, h dy, h dx^2, h dx dy, h dy^2 (dx, dy = centre - pixel)
-            const float M1 = o * g2[0], M2 = o * g2[1], M3 = o * g2[2], M4 = o * g2[3], M5 = o * g2[4];
-            const float g_o = g2[5], g_zd = g2[9];
+            // slots 0..5, each in two parts, hold pixel sums of p = dL/dpower: p dx, p dy, p dx^2, p dx dy,
+            // p dy^2 (dx, dy = centre - pixel) and p itself, o dL/do (a visible pair's o >= alpha_min)
+            const float M1 = g2[0] + g2[10], M2 = g2[1] + g2[11], M3 = g2[2] + g2[12], M4 = g2[3] + g2[13];
+            const float M5 = g2[4] + g2[14], g_o = (g2[5] + g2[15]) / o, g_zd = g2[9];
             const ags_camera cam = opaque_ptr(a.cams)[b];
             const float* R = cam.R;
             float x, y, z;

@@ -1,36 +1,45 @@
 // Tile rasterisation of all views in one launch: forward compositing and its adjoint.
 //
 // A workgroup owns one T x T tile of one view (the global tile id selects the view), so a
-// rig's views and a set of submaps share one launch.  The tile's depth-ordered Gaussian
-// list is streamed through LDS in batches; every lane reads the same record (LDS
-// broadcast) and composites its pixel(s) front to back (Sec. III-B, standard 3DGS):
+// rig's views and a set of submaps share one launch.  Its waves own 8 x 8 blocks of the tile (one
+// pixel a lane) or 8 x 16 blocks (two, eight rows apart) and work independently: a wave streams
+// the tile's depth-ordered list 64 entries at a time, one per lane, keeps those whose alpha >=
+// alpha_min ellipse reaches its own block (block_reached), packs them in order into LDS rows of its
+// own and composites them front to back (Sec. III-B, standard 3DGS):
 //   power = -1/2 (a dx^2 + c dy^2) - b dx dy, (dx, dy) = (u, v) - pixel centre
 //   alpha = min(alpha_max, o e^power), skipped when power > 0 or alpha < alpha_min
 //   T' = T (1 - alpha); stop (excluding this Gaussian) when T' < t_min
 //   C += alpha T rgb; D += alpha T z; T = T'
 // and the accumulated alpha A = sum alpha T is written as 1 - T_final (the same sum, not
-// accumulated in the loop).
-// A workgroup stops fetching batches once every pixel has stopped, and a wave whose lanes
-// have all stopped skips the rest of a batch.  The forward keeps 8 bytes per pixel
-// (final T and the list position of the last contributor) so the backward recomputes
-// transmittance instead of storing per-pixel blend lists.
+// accumulated in the loop).  A wave ends when its pixels have stopped; there is no barrier in
+// the loops.  The forward keeps 8 bytes per pixel (final T and the list position of the last
+// contributor) so the backward recomputes transmittance instead of storing per-pixel blend
+// lists.
 //
 // The backward walks the list back to front from the last contributor, recovering
 // T_k = T_{k+1} / (1 - alpha_k) and accumulating suffix sums S = sum_{j>k} w_j f_j:
 //   dL/dalpha_k = T_k (gC . c_k + gD z_k + gA)
 //                 - (gC . S^C + gD S^D + gA S^A + T_final gC . bg) / (1 - alpha_k)
 // (the bracket is kept as one running sum U), then chains through alpha = o e^power (unless
-// clamped) to the opacity, h = dL/do = e^power dL/dalpha, and to dL/dpower = o h, of which
-// it keeps five pixel moments without the factor o (sum h dx, h dy, h dx^2, h dx dy,
-// h dy^2); the projection backward applies o and turns them into the centre and conic
-// adjoints.  dL/drgb_k = w_k gC, dL/dz_k = w_k gD.  The ten per-Gaussian
-// sums of a wave are reduced with a transposing butterfly to ten lanes.  With LDS batches of
-// at most 64 records those lanes add them into the batch's LDS accumulator of that Gaussian
-// (the workgroup's waves merge there), and after the batch one global atomic per (Gaussian,
-// non-zero sum) adds the workgroup's total into the pair's 64-byte adjoint row, so each row
-// is updated once per tile; with larger batches (where the accumulator's LDS would cut the
-// number of resident workgroups) one atomic instruction of the ten lanes per wave updates
-// the row.
+// clamped) to p = dL/dpower = alpha dL/dalpha, of which it keeps the sum (= o dL/do) and five pixel
+// moments (sum p dx, p dy, p dx^2, p dx dy, p dy^2); the projection backward turns them into the
+// opacity, centre and conic adjoints.  dL/drgb_k = w_k gC, dL/dz_k = w_k gD.  The ten per-Gaussian
+// sums of a wave are reduced over its lanes (wave_column_sums) and one atomic instruction of ten
+// lanes adds them into the pair's 64-byte adjoint row.
+//
+// What bounds both kernels is vector instruction issue.  Measured on one SIMD with eight waves, a
+// wave64 instruction takes: 2 cycles for add / mul / fma f32 and moves with vector operands, 4 with a
+// scalar operand and for compares, selects, min / max and DPP, 8 for exp / rcp and the lane swaps;
+// scalar instructions issue one per 4 cycles and a 16-byte LDS read of one address by all lanes
+// takes 5 of the CU's LDS cycles.  The loops are built for those costs: the per-pixel tests that
+// only an odd record needs (p2 <= 0, the alpha clamp) are made only for chunks that hold one, keep
+// decisions stay in scalar lane masks, and the records are read from consecutive LDS rows instead
+// of by scalar bit scans (which bound an earlier form of the forward at 85 % scalar issue).
+// 8 x 16 blocks share dx and the record reads between two pixels and halve the per-chunk work, 8 x 8
+// blocks give a launch twice the waves, each with half the serial work: launches of at least 8192
+// waves of 8 x 16 blocks (what the chip holds) take the former, others the latter (wide_blocks).
+#include <type_traits>
+
 #include "common.h"
 
 namespace ags {
@@ -53,314 +62,414 @@ __device__ __forceinline__ TileCoord tile_coord(const ViewTable& vt, int tile) {
     return c;
 }
 
-// Each wave owns a rectangular block of the tile: 8 columns x 8 PPT rows when the tile has
-// enough waves for its 8-wide column strips, else the full tile width.  Lane l covers
-// column l % BW and PPT vertically adjacent rows.  The per-record wave mask below lets a
-// whole wave skip Gaussians whose footprint box misses its block.
-template <int T, int PPT>
-struct WaveGrid {
-    static constexpr int NT = T * T / PPT;
-    static constexpr int NW = NT / 64;
-    static constexpr int BW = (NW >= T / 8) ? 8 : T;
-    static constexpr int COLS = T / BW;
-    static constexpr int BH = 64 * PPT / BW;
-    static_assert(COLS * (T / BH) == NW, "wave blocks must tile the tile");
-};
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kChunk = 64;  // list entries a wave takes at a time
 
-// BLOCKS = false: row strips (thread t covers column t % T and PPT rows), used by the
-// forward, where full-width rows keep the output writes coalesced.  BLOCKS = true: the wave
-// blocks above, used by the backward together with the wave mask.
-template <int T, int PPT, bool BLOCKS>
-__device__ __forceinline__ void pixel_of(int t, int k, int& x, int& y) {
-    if (BLOCKS) {
-        using G = WaveGrid<T, PPT>;
-        const int w = t >> 6, l = t & 63;
-        x = (w % G::COLS) * G::BW + l % G::BW;
-        y = (w / G::COLS) * G::BH + (l / G::BW) * PPT + k;
-    } else {
-        x = t % T;
-        y = (t / T) * PPT + k;
-    }
+// Whether the alpha >= alpha_min ellipse of the record (u, v, a, b | c, o) may reach the pixel
+// centres of the block whose first one is (X0, Y0) and whose last one is (X0 + wx, Y0 + wy).  The
+// quadratic form is convex with its minimum at the centre, so its minimum over the rectangle lies
+// on a side facing the centre: the nearer vertical and the nearer horizontal side, each at its own
+// minimiser clamped to the side.  The level is 2 ln(o / alpha_min) itself (the binning rebuilds it from
+// the footprint box, whose determinant cancels for a thin ellipse), widened by 2e-3 of itself, 1e-3,
+// and the rounding of the form at the far corner (its terms may cancel); NaN keeps the record.
+__device__ __forceinline__ bool block_reached(const float4& r0, float c, float o, float inv_amin, float X0, float Y0,
+                                              float wx, float wy) {
+    const float a = r0.z, b = r0.w, b2 = 2.f * b;
+    const float lx = X0 - r0.x, hx = lx + wx, ly = Y0 - r0.y, hy = ly + wy;
+    const float fx = fmaxf(fabsf(lx), fabsf(hx)), fy = fmaxf(fabsf(ly), fabsf(hy));
+    const float tau2 = 2.004f * __logf(o * inv_amin) + 1e-3f + 2e-6f * (a * fx * fx + c * fy * fy);
+    const float X = __builtin_amdgcn_fmed3f(0.f, lx, hx), Y = __builtin_amdgcn_fmed3f(0.f, ly, hy);
+    const float y = __builtin_amdgcn_fmed3f(-b * __builtin_amdgcn_rcpf(c) * X, ly, hy);
+    const float x = __builtin_amdgcn_fmed3f(-b * __builtin_amdgcn_rcpf(a) * Y, lx, hx);
+    const float q1 = X * (a * X + b2 * y) + c * y * y;
+    const float q2 = x * (a * x + b2 * Y) + c * Y * Y;
+    return !(q1 > tau2 && q2 > tau2);
 }
 
-// Bit w set when the record's pixel footprint box (the binning rectangle, clamped to the
-// image) intersects the pixels of wave w in the tile at (px0, py0): its block (BLOCKS) or
-// its rows (row strips).  (The forward does not use it: testing it per entry cost more
-// than the skipped entries saved there.)
-template <int T, int PPT, bool BLOCKS>
-__device__ __forceinline__ uint32_t wave_mask(float u, float v, float ex, float ey, int W, int H, int px0,
-                                              int py0) {
-    using G = WaveGrid<T, PPT>;
-    const float fx0 = floorf(__fsub_rn(__fsub_rn(u, ex), 0.5f));
-    const float fx1 = ceilf(__fsub_rn(__fadd_rn(u, ex), 0.5f));
-    const float fy0 = floorf(__fsub_rn(__fsub_rn(v, ey), 0.5f));
-    const float fy1 = ceilf(__fsub_rn(__fadd_rn(v, ey), 0.5f));
-    // relative to the tile, clamped to [-1, T]
-    const int x0 = (int)fminf(fmaxf(fx0 - (float)px0, -1.f), (float)T);
-    const int x1 = (int)fminf(fmaxf(fx1 - (float)px0, -1.f), (float)T);
-    const int y0 = (int)fminf(fmaxf(fy0 - (float)py0, -1.f), (float)T);
-    const int y1 = (int)fminf(fmaxf(fy1 - (float)py0, -1.f), (float)T);
-    uint32_t m = 0;
-    if (BLOCKS) {
-#pragma unroll
-        for (int w = 0; w < G::NW; ++w) {
-            const int bx0 = (w % G::COLS) * G::BW, by0 = (w / G::COLS) * G::BH;
-            if (x0 <= bx0 + G::BW - 1 && x1 >= bx0 && y0 <= by0 + G::BH - 1 && y1 >= by0) m |= 1u << w;
-        }
-    } else {
-        constexpr int RW = 64 * PPT / T;  // rows per wave (>= T: one wave holds the tile)
-        if (x0 <= T - 1 && x1 >= 0) {
-#pragma unroll
-            for (int w = 0; w < G::NW; ++w)
-                if (y0 <= w * RW + RW - 1 && y1 >= w * RW) m |= 1u << w;
-        }
-    }
-    (void)W;
-    (void)H;
-    return m;
+// Whether the exponent of a record may round above 0 or its alpha reach the clamp, so that both
+// tests have to be made per pixel: a conic (A', B', C', pre-scaled) that is not definite by a margin
+// far above rounding, an opacity above alpha_max, NaN.
+__device__ __forceinline__ bool needs_tests(float A, float B, float C, float o, float amax) {
+    return !(o <= amax && A < 0.f && C < 0.f && B * B < 3.9999f * (A * C));
 }
 
-// Copy record q into LDS in the form the per-pixel loops use: the conic (a, b, c) becomes
-// log2(e) (-a/2, -b, -c/2), so the exponent in base 2, p2 = dx (A' dx + B' dy) + C' dy^2,
-// costs five operations and e^power = exp2(p2) is one instruction; the footprint extent is
-// replaced by the exponent floor log2(alpha_min / o) - kPreTestMargin and by the mask of wave
-// blocks its footprint box touches.  Both kernels keep a (pixel, Gaussian) pair exactly when
-// p2 <= 0 and alpha = min(alpha_max, o exp2(p2)) >= alpha_min, in float32, so their decisions
-// agree; the backward tests the exponent floor first to skip whole entries.  A kept pair has
-// o exp2(p2) >= alpha_min, so p2 >= log2(alpha_min / o) less the float32 rounding of the
-// product and of exp2 (a few 1e-7), and the computed floor is within ~1e-6 of the exact
-// log2: the 1e-4 margin keeps every kept pair above the floor, so the pre-test never
-// changes a decision; every skipped pair has alpha < alpha_min.
-// LDS layout (64 B, read at non-negative offsets from one per-lane address):
-//   [0] = (wave mask bits, r, g, b) in the backward, (z, r, g, b) in the forward,
-//   [1] = (u, v, -a/2 log2e, -b log2e), [2] = (-c/2 log2e, o, z, exponent floor),
-//   [3] = (pair id, z^2, address of the pair's 2D adjoint row (backward)).
-// The forward reads 24 bytes of an entry ([1] and the first half of [2]) before its keep
-// test and [0] only for a pixel that takes the Gaussian.
-struct alignas(16) SRec {
-    float4 m, g0, g1;
-    uint32_t q;
-    float z2;
-    float* row;  // the pair's 2D adjoint row (backward)
-};
-
-constexpr float kPreTestMargin = 1e-4f;
-template <int T, int PPT, bool BLOCKS>
-__device__ __forceinline__ uint32_t stage_record(const float* records, uint32_t q, float amin, int W, int H,
-                                                 int px0, int py0, SRec& dst, float* grad2d = nullptr) {
-    const float4* r = reinterpret_cast<const float4*>(records + (long long)q * kRecFloats);
-    const float4 r0 = r[0], r1 = r[1], r2 = r[2];
-    constexpr float kLog2e = 1.4426950408889634f;
-    const uint32_t m = BLOCKS ? wave_mask<T, PPT, BLOCKS>(r0.x, r0.y, r1.w, r2.x, W, H, px0, py0) : ~0u;
-    dst.m = make_float4(BLOCKS ? __uint_as_float(m) : r1.z, r2.y, r2.z, r2.w);
-    dst.g0 = make_float4(r0.x, r0.y, -0.5f * kLog2e * r0.z, -kLog2e * r0.w);
-    dst.g1 = make_float4(-0.5f * kLog2e * r1.x, r1.y, r1.z, __log2f(amin / r1.y) - kPreTestMargin);
-    dst.q = q;
-    dst.z2 = r1.z * r1.z;
-    if (BLOCKS) dst.row = grad2d + (long long)q * kGrad2dStride;
-    return m;
+// The base-2 exponent A' dx^2 + B' dx dy + C' dy^2 in one fixed order of roundings, so that the
+// forward and the backward decide on the same bits.
+__device__ __forceinline__ float exponent2(float A, float B, float C, float dx, float dy) {
+    return __builtin_fmaf(dy, dy * C, dx * __builtin_fmaf(dx, A, dy * B));
 }
 
-// Makes the record's fields live at this point, so all of its LDS reads are issued together
-// (one round trip) instead of being deferred past the wave-uniform tests that use them.
-__device__ __forceinline__ void use_record(const float4& a, const float4& b) {
-    asm volatile("" ::"v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w));
+// Lane mask of a <= b, and this lane's bit of a wave-uniform mask.
+__device__ __forceinline__ unsigned long long le_mask(float a, float b) {
+    return __builtin_amdgcn_fcmpf(a, b, 5);  // ordered, less or equal
 }
-__device__ __forceinline__ void use_record(const float4& a, const float4& b, const float4& c) {
-    use_record(a, b);
-    asm volatile("" ::"v"(c.x), "v"(c.y), "v"(c.z), "v"(c.w));
+__device__ __forceinline__ bool lane_of(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ int rank_in(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Keeps a value in a vector register from here on, so an LDS address derived from it is
-// advanced with one vector add per iteration instead of being rebuilt from scalars.
+// Keeps a value in a vector register from here on.
 template <typename V>
 __device__ __forceinline__ void in_vgpr(V& v) {
     asm volatile("" : "+v"(v));
 }
 
-__device__ __forceinline__ float power_of(const float4& r0, const float4& r1, float dx, float dy) {
-    return dx * (r0.z * dx + r0.w * dy) + r1.x * dy * dy;
+// Issue priority of a wave by the entries it has ahead of it.  Eight waves share a SIMD, so at equal
+// priority a tile with a long list advances at an eighth of the SIMD's rate and ends after the rest of
+// the launch, although the longest lists start first (see kWorkStrip): raster backward of a
+// 2M-Gaussian 4-view step 534 -> 475 us, of a 22-view 2.9M sub-map step 1217 -> 1180 us.
+__device__ __forceinline__ void prio_by_length(int n) {
+    if (n >= 512) __builtin_amdgcn_s_setprio(3);
+    else if (n >= 256) __builtin_amdgcn_s_setprio(2);
+    else if (n >= 128) __builtin_amdgcn_s_setprio(1);
 }
 
-// S2: also output the rendered depth variance sum w z^2 - (sum w z)^2 (rendered-variance
-// LiDAR term), accumulated without cancellation: the weighted scatter S about the running
-// normalised mean m (A' = A + w, m' = m + (z - m) w / A', S' = S + w (z - m)(z - m')), then
-// sum w z^2 - (A m)^2 = S + A (1 - A) m^2 with 1 - A = the final transmittance.
-template <int T, int PPT, int M, bool S2>
-__global__ __launch_bounds__(T* T / PPT) void raster_fwd_kernel(RasterArgs a) {
-    constexpr int NT = T * T / PPT;
-    __shared__ SRec srec[M];
+// A wave's loads of a list: lane l holds the record of one entry.
+struct Rec {
+    float4 a, b, c;  // u v a b | c o z ex | ey r g b
+};
+__device__ __forceinline__ Rec load_rec(const float* records, uint32_t q) {
+    const float4* r = reinterpret_cast<const float4*>(records + (long long)q * kRecFloats);
+    return {r[0], r[1], r[2]};
+}
+
+// A wave's LDS rows: the records of a chunk that reach its block, in list order, then PAD fillers
+// (opacity 0) for the last group; the conic (a, b, c) becomes log2(e) (-a/2, -b, -c/2), so that the
+// exponent in base 2 is exponent2 and e^power one instruction.
+template <int PAD>
+struct Rows {
+    float4 g[kChunk + PAD];    // u v A' B'
+    float4 col[kChunk + PAD];  // r g b z
+    float2 co[kChunk + PAD];   // C' o
+    uint32_t pos[kChunk + PAD];
+    // Packs the lanes' records with `in` set and returns how many there are; `slow` if any of them
+    // needs the per-pixel tests.
+    __device__ __forceinline__ int pack(const Rec& r, bool in, uint32_t position, float amax, bool& slow) {
+        const unsigned long long im = __builtin_amdgcn_ballot_w64(in);
+        const int n = __popcll(im), at = rank_in(im);
+        const float A = -0.5f * kLog2e * r.a.z, B = -kLog2e * r.a.w, C = -0.5f * kLog2e * r.b.x;
+        slow = __builtin_amdgcn_ballot_w64(in && needs_tests(A, B, C, r.b.y, amax)) != 0ull;
+        if (in) {
+            g[at] = make_float4(r.a.x, r.a.y, A, B);
+            co[at] = make_float2(C, r.b.y);
+            col[at] = make_float4(r.c.y, r.c.z, r.c.w, r.b.z);
+            pos[at] = position;
+        }
+        const int lane = __lane_id();
+        if (lane < PAD) {
+            g[n + lane] = col[n + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+            co[n + lane] = make_float2(0.f, 0.f);
+            pos[n + lane] = 0u;
+        }
+        __builtin_amdgcn_wave_barrier();
+        return n;
+    }
+};
+
+// The rendered depth variance sum w z^2 - (sum w z)^2 (rendered-variance LiDAR term), accumulated
+// without cancellation: the weighted scatter S about the running normalised mean m (A' = A + w,
+// m' = m + (z - m) w / A', S' = S + w (z - m)(z - m')), then sum w z^2 - (A m)^2 =
+// S + A (1 - A) m^2 with 1 - A = the final transmittance.  One fixed order of roundings for both block
+// shapes.
+struct Scatter {
+    float A = 0.f, m = 0.f, S = 0.f;
+    __device__ __forceinline__ void add(float w, float z) {
+#pragma clang fp contract(off)
+        A += w;
+        const float dz = z - m;
+        m = __builtin_fmaf(dz, w * __builtin_amdgcn_rcpf(A), m);
+        S = __builtin_fmaf(w * dz, z - m, S);
+    }
+    __device__ __forceinline__ float variance(float T) const { return __builtin_fmaf(A * T * m, m, S); }
+};
+
+__device__ __forceinline__ void write_pixel(const RasterArgs& a, const TileCoord& tc, int x, int y, float r, float g,
+                                            float b, float D, float T, uint32_t last, const Scatter* var) {
+    const long long plane = (long long)tc.W * tc.H, p = (long long)y * tc.W + x, gp = tc.pix0 + p;
+    float* rgb = a.rgb + 3 * tc.pix0;
+    rgb[p] = r + T * a.st.bg0;
+    rgb[plane + p] = g + T * a.st.bg1;
+    rgb[2 * plane + p] = b + T * a.st.bg2;
+    a.depth[gp] = D;
+    if (var) a.depth_var[gp] = var->variance(T);
+    a.alpha[gp] = 1.f - T;
+    a.t_final[gp] = T;
+    a.last[gp] = last;
+    if (a.zero_px[0]) a.zero_px[0][gp] = 0.f;
+    if (a.zero_px[1]) a.zero_px[1][gp] = 0.f;
+}
+
+// ------------------------------------------------------------------------- forward
+//
+// 8 x 8 blocks, one pixel a lane, four entries a step: their exponents are formed side by side and
+// only T is carried from one to the next, because the launches that come here have too few waves to
+// hide a serial chain (one 960 x 600 view over 300k Gaussians: 102 -> 47 us; two 161 x 119 views over
+// 4k: 22 -> 12 us).  The colour is a contraction over the entries, C[ch][pixel] += c[ch] w[pixel], which
+// v_mfma_f32_4x4x1_16b_f32 does with the pixel's four sums in its own lane: one LDS read a step gives
+// the colours of all four entries, where broadcast reads kept the LDS 80 % busy.  It rounds like the
+// four fmas it replaces.  S2: also output the rendered depth variance.
+template <int T, bool S2>
+__global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
+    constexpr int NW = T * T / 64, COLS = T / 8, GRP = 4;
+    __shared__ Rows<GRP> rows[NW];
     const uint32_t wt = a.work[blockIdx.x];
-    if (wt == kNoTile) return;  // padding of a shorter XCD list (whole workgroup)
+    if (wt == kNoTile) return;  // padding of a shorter XCD list
     const int tile = (int)wt;
     const TileCoord tc = tile_coord(a.vt, tile);
     const uint32_t start = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile]);
     const uint32_t end = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile + 1]);
-    const int tid = threadIdx.x;
+    const int lane = __lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Rows<GRP>& my = rows[wave];
 
-    // A pixel that has stopped (or lies outside the image) gets cx = +inf: its exponent is
-    // then -inf (or NaN), below every threshold, so it keeps no further Gaussian without a
-    // separate flag test.
-    constexpr float kStopped = __builtin_huge_valf();
-    float cx[PPT], cy[PPT], Tr[PPT], C0[PPT], C1[PPT], C2[PPT], D[PPT], A[PPT], Mn[PPT], Sc[PPT];
-    uint32_t last[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        int lx, ly;
-        pixel_of<T, PPT, false>(tid, k, lx, ly);
-        const int px = tc.px0 + lx, py = tc.py0 + ly;
-        cx[k] = (px < tc.W && py < tc.H) ? (float)px + 0.5f : kStopped;
-        cy[k] = (float)py + 0.5f;
-        Tr[k] = 1.f;
-        C0[k] = C1[k] = C2[k] = D[k] = A[k] = Mn[k] = Sc[k] = 0.f;
-        last[k] = 0;
-    }
+    const int bx = tc.px0 + (wave % COLS) * 8, by = tc.py0 + (wave / COLS) * 8;
+    const int px = bx + (lane & 7), py = by + (lane >> 3);
+    const float cx = (float)px + 0.5f, cy = (float)py + 0.5f;
+    const float X0 = (float)bx + 0.5f, Y0 = (float)by + 0.5f;
+    const bool inside = px < tc.W && py < tc.H;
+    unsigned long long open = __builtin_amdgcn_ballot_w64(inside);  // lanes whose pixel has not stopped
+    float Tr = 1.f;
+    f32x4 C = {0.f, 0.f, 0.f, 0.f};  // r, g, b, expected depth
+    Scatter var;
+    uint32_t last = 0;
     const float amin = a.st.alpha_min, tmin = a.st.t_min;
     const float amax = __builtin_canonicalizef(a.st.alpha_max);
+    const float inv_amin = 1.f / amin;
 
-    for (uint32_t bs = start; bs < end; bs += M) {
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) any |= cx[k] != kStopped;
-        if (__syncthreads_count(any) == 0) break;
-#pragma unroll
-        for (int l = tid; l < M; l += NT) {
-            const uint32_t e = bs + l;
-            if (e < end)
-                stage_record<T, PPT, false>(a.records, a.tile_pairs[e], amin, tc.W, tc.H, tc.px0, tc.py0,
-                                            srec[l]);
+    // a chunk's records are loaded while the chunk before it is composited, its pair ids one chunk
+    // earlier still
+    auto id_of = [&](uint32_t e) { return a.tile_pairs[e < end ? e : end - 1]; };
+    Rec next = {};
+    uint32_t nq = 0;
+    if (start < end) {
+        next = load_rec(a.records, id_of(start + lane));
+        nq = id_of(start + kChunk + lane);
+    }
+    for (uint32_t bs = start; bs < end && open != 0ull; bs += kChunk) {
+        const Rec r = next;
+        if (bs + kChunk < end) {
+            next = load_rec(a.records, nq);
+            nq = id_of(bs + 2 * kChunk + lane);
         }
-        __syncthreads();
-        const uint32_t bend = end - bs > (uint32_t)M ? bs + M : end;
-        const char* sbase = reinterpret_cast<const char*>(srec);
-        uint32_t off = 0;  // byte offset of record e - bs in LDS
-        in_vgpr(off);
-        // entries in groups of eight: the later records are read at immediate offsets from the
-        // first's LDS address, so the address advances once per group, and the wave's early
-        // exit is tested once per group (entries past a wave's stop keep nothing: a stopped
-        // pixel's exponent is -inf or NaN)
-        auto entry = [&](const SRec& r, uint32_t e) {
-            const float4 r0 = r.g0;
-            const float2 r1 = *reinterpret_cast<const float2*>(&r.g1);  // (C', o)
-            use_record(r0, make_float4(r1.x, r1.y, 0.f, 0.f));
+        const uint32_t e = bs + lane;
+        const bool in = e < end && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, Y0, 7.f, 7.f);
+        bool slow;
+        const int n = my.pack(r, in, e - start + 1, amax, slow);
+        int lastc = -1;  // the last contributor's row in this chunk
+        auto run = [&](auto tests) {
+            int row = 0;
+            in_vgpr(row);
+            for (int g = 0; g < n && open != 0ull; g += GRP, row += GRP) {
+                // lanes 4 i .. 4 i + 3 hold the channels of the step's entry i (i < 4)
+                const float colv = reinterpret_cast<const float*>(my.col + g)[lane & 15];
+                float4 r0[GRP];
+                float2 r1[GRP];
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                // one predicate, one branch: the exp is cheap next to divergent control
-                const float dx = r0.x - cx[k], dy = r0.y - cy[k];
-                const float p2 = dx * (r0.z * dx + r0.w * dy) + r1.x * dy * dy;
-                const float alpha = fminf(amax, r1.y * __builtin_amdgcn_exp2f(p2));
-                const bool keep = p2 <= 0.f && alpha >= amin;
-                if (keep) {
-                    // stop (once per pixel) before a Gaussian that would take T below t_min;
-                    // the tested T (1 - alpha), one rounding, is the next T
-                    const float Tn = __builtin_fmaf(-alpha, Tr[k], Tr[k]);
-                    const bool go = Tn >= tmin;
-                    cx[k] = go ? cx[k] : kStopped;  // +inf marks the pixel stopped
-                    in_vgpr(cx[k]);                 // one select here, not moves in both branches
-                    if (go) {
-                        const float4 rc = r.m;  // (z, r, g, b)
-                        const float w = alpha * Tr[k];
-                        C0[k] += w * rc.y;
-                        C1[k] += w * rc.z;
-                        C2[k] += w * rc.w;
-                        D[k] += w * rc.x;
-                        if (S2) {
-                            A[k] += w;
-                            const float dz = rc.x - Mn[k];
-                            Mn[k] += dz * (w * __builtin_amdgcn_rcpf(A[k]));
-                            Sc[k] += w * dz * (rc.x - Mn[k]);
+                for (int i = 0; i < GRP; ++i) {
+                    r0[i] = my.g[g + i];
+                    r1[i] = my.co[g + i];
+                }
+                float al[GRP];
+                unsigned long long kp[GRP];  // lanes that keep the pair, open or not
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+                    const float p2 = exponent2(r0[i].z, r0[i].w, r1[i].x, r0[i].x - cx, r0[i].y - cy);
+                    al[i] = r1[i].y * __builtin_amdgcn_exp2f(p2);
+                    if (decltype(tests)::value) al[i] = fminf(amax, al[i]);
+                    kp[i] = le_mask(amin, al[i]);
+                    if (decltype(tests)::value) kp[i] &= le_mask(p2, 0.f);
+                    in_vgpr(al[i]);  // formed here, not inside the branches below
+                }
+                // the entry index is an immediate of the matrix instruction
+                auto blend = [&](auto entry) {
+                    constexpr int i = decltype(entry)::value;
+                    const unsigned long long km = kp[i] & open;
+                    if (km == 0ull) return;  // wave-uniform
+                    // stop before a Gaussian that would take T below t_min; T (1 - alpha), one
+                    // rounding, is the next T
+                    const float Tn = __builtin_fmaf(-al[i], Tr, Tr);
+                    const unsigned long long go = le_mask(tmin, Tn) & km;
+                    open &= ~(km ^ go);
+                    const float w = lane_of(go) ? al[i] * Tr : 0.f;
+                    C = __builtin_amdgcn_mfma_f32_4x4x1f32(colv, w, C, 4, i, 0);
+                    if (lane_of(go)) {
+                        if (S2) var.add(w, my.col[g + i].w);
+                        Tr = Tn;
+                        lastc = row + i;
+                    }
+                };
+                blend(std::integral_constant<int, 0>{});
+                blend(std::integral_constant<int, 1>{});
+                blend(std::integral_constant<int, 2>{});
+                blend(std::integral_constant<int, 3>{});
+            }
+        };
+        if (slow) run(std::true_type{});
+        else run(std::false_type{});
+        if (lastc >= 0) last = my.pos[lastc];
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (inside) write_pixel(a, tc, px, py, C[0], C[1], C[2], C[3], Tr, last, S2 ? &var : nullptr);
+}
+
+// 8 x 16 blocks, two pixels a lane eight rows apart (the same dx), two entries a step, plain fmas: one
+// read of a record serves two pixels, which keeps the LDS behind the vector units.  4-view 1280 x 800
+// step over 1M Gaussians 195 -> 173 us, over 2M 246 -> 204 us, 22 views over 2.9M 507 -> 480 us.
+// No prefetch: it costs two of eight waves a SIMD (rig step 177 -> 192 us).
+template <int T, bool S2>
+__global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a) {
+    constexpr int NW = T * T / 128, COLS = T / 8, GRP = 2, PPT = 2;
+    __shared__ Rows<GRP> rows[NW];
+    const uint32_t wt = a.work[blockIdx.x];
+    if (wt == kNoTile) return;  // padding of a shorter XCD list
+    const int tile = (int)wt;
+    const TileCoord tc = tile_coord(a.vt, tile);
+    const uint32_t start = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile]);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile + 1]);
+    const int lane = __lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Rows<GRP>& my = rows[wave];
+    const int bx = tc.px0 + (wave % COLS) * 8, by = tc.py0 + (wave / COLS) * 16;
+    const int px = bx + (lane & 7), py = by + (lane >> 3);
+    const float cx = (float)px + 0.5f;
+    float cy[PPT], Tr[PPT], C0[PPT], C1[PPT], C2[PPT], D[PPT];
+    Scatter var[PPT];
+    uint32_t last[PPT];
+    unsigned long long open[PPT];  // lanes whose pixel is in the image and has not stopped
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        cy[k] = (float)(py + 8 * k) + 0.5f;
+        open[k] = __builtin_amdgcn_ballot_w64(px < tc.W && py + 8 * k < tc.H);
+        Tr[k] = 1.f;
+        C0[k] = C1[k] = C2[k] = D[k] = 0.f;
+        last[k] = 0;
+    }
+    prio_by_length((int)(end - start));
+    const float amin = a.st.alpha_min, tmin = a.st.t_min;
+    const float amax = __builtin_canonicalizef(a.st.alpha_max);
+    const float inv_amin = 1.f / amin;
+    const float X0 = (float)bx + 0.5f, Y0 = (float)by + 0.5f;
+
+    for (uint32_t bs = start; bs < end && (open[0] | open[1]) != 0ull; bs += kChunk) {
+        const uint32_t e = bs + lane;
+        const Rec r = load_rec(a.records, a.tile_pairs[e < end ? e : end - 1]);
+        // a half whose pixels have stopped takes no more entries
+        const float top = open[0] ? Y0 : Y0 + 8.f, span = open[0] && open[1] ? 15.f : 7.f;
+        const bool in = e < end && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, top, 7.f, span);
+        bool slow;
+        const int n = my.pack(r, in, e - start + 1, amax, slow);
+        int lastc[PPT] = {-1, -1};  // the last contributor's row in this chunk
+        auto run = [&](auto tests) {
+            int row = 0;
+            in_vgpr(row);
+            for (int g = 0; g < n; g += GRP, row += GRP) {
+                float4 r0[GRP], rc[GRP];
+                float2 r1[GRP];
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+                    r0[i] = my.g[g + i];
+                    r1[i] = my.co[g + i];
+                    rc[i] = my.col[g + i];
+                }
+                float al[GRP][PPT];
+                unsigned long long kp[GRP][PPT];  // lanes that keep the pair, open or not
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+                    const float dx = r0[i].x - cx;
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        const float p2 = exponent2(r0[i].z, r0[i].w, r1[i].x, dx, r0[i].y - cy[k]);
+                        al[i][k] = r1[i].y * __builtin_amdgcn_exp2f(p2);
+                        if (decltype(tests)::value) al[i][k] = fminf(amax, al[i][k]);
+                        kp[i][k] = le_mask(amin, al[i][k]);
+                        if (decltype(tests)::value) kp[i][k] &= le_mask(p2, 0.f);
+                        in_vgpr(al[i][k]);  // formed here, not inside the branches below
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        const unsigned long long km = kp[i][k] & open[k];
+                        if (km == 0ull) continue;  // wave-uniform
+                        // the stop test as above
+                        const float Tn = __builtin_fmaf(-al[i][k], Tr[k], Tr[k]);
+                        const unsigned long long go = le_mask(tmin, Tn) & km;
+                        open[k] &= ~(km ^ go);
+                        if (lane_of(go)) {
+                            const float w = al[i][k] * Tr[k];
+                            C0[k] = __builtin_fmaf(w, rc[i].x, C0[k]);
+                            C1[k] = __builtin_fmaf(w, rc[i].y, C1[k]);
+                            C2[k] = __builtin_fmaf(w, rc[i].z, C2[k]);
+                            D[k] = __builtin_fmaf(w, rc[i].w, D[k]);
+                            if (S2) var[k].add(w, rc[i].w);
+                            Tr[k] = Tn;
+                            lastc[k] = row + i;
                         }
-                        Tr[k] = Tn;
-                        last[k] = e - start + 1;
                     }
                 }
             }
         };
-        auto wave_live = [&]() {
-            bool live = false;
+        if (slow) run(std::true_type{});
+        else run(std::false_type{});
 #pragma unroll
-            for (int k = 0; k < PPT; ++k) live |= cx[k] != kStopped;
-            return __ballot(live) != 0ull;  // wave-uniform: false once every pixel has stopped
-        };
-        for (uint32_t e = bs; e < bend; e += 8, off += 8 * sizeof(SRec)) {
-            if (!wave_live()) break;
-            entry(*reinterpret_cast<const SRec*>(sbase + off), e);
-#pragma unroll
-            for (int g = 1; g < 8; ++g) {
-                if (e + g == bend) break;
-                entry(*reinterpret_cast<const SRec*>(sbase + off + g * sizeof(SRec)), e + g);
-            }
-        }
-        __syncthreads();
+        for (int k = 0; k < PPT; ++k)
+            if (lastc[k] >= 0) last[k] = my.pos[lastc[k]];
+        __builtin_amdgcn_wave_barrier();
     }
-    const long long plane = (long long)tc.W * tc.H;
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        int lx, ly;
-        pixel_of<T, PPT, false>(tid, k, lx, ly);
-        if (tc.px0 + lx >= tc.W || tc.py0 + ly >= tc.H) continue;
-        const long long p = (long long)(tc.py0 + ly) * tc.W + (tc.px0 + lx);
-        const long long gp = tc.pix0 + p;
-        float* rgb = a.rgb + 3 * tc.pix0;
-        rgb[p] = C0[k] + Tr[k] * a.st.bg0;
-        rgb[plane + p] = C1[k] + Tr[k] * a.st.bg1;
-        rgb[2 * plane + p] = C2[k] + Tr[k] * a.st.bg2;
-        a.depth[gp] = D[k];
-        if (S2) a.depth_var[gp] = Sc[k] + A[k] * Tr[k] * Mn[k] * Mn[k];
-        a.alpha[gp] = 1.f - Tr[k];
-        a.t_final[gp] = Tr[k];
-        a.last[gp] = last[k];
-        if (a.zero_px[0]) a.zero_px[0][gp] = 0.f;
-        if (a.zero_px[1]) a.zero_px[1][gp] = 0.f;
-    }
+    for (int k = 0; k < PPT; ++k)
+        if (px < tc.W && py + 8 * k < tc.H)
+            write_pixel(a, tc, px, py + 8 * k, C0[k], C1[k], C2[k], D[k], Tr[k], last[k], S2 ? &var[k] : nullptr);
 }
 
-// GA: the upstream adjoint has an alpha term (dL/dA); the fused loss never has one.
-// S2: the loss has an adjoint for the second depth moment sum w z^2 (rendered variance).
-template <int T, int PPT, int M, bool GA, bool S2>
+// ------------------------------------------------------------------------- backward
+//
+// PPT pixels a lane (8 x 8 PPT blocks), GRP entries a step: the exponents of a step are formed side by
+// side, then each entry that some lane keeps runs its adjoint and reduction.  Two pixels a lane
+// share dx, the record reads and one reduction (a third of the issue cycles): rig step 500 -> 430 us,
+// over 2M Gaussians 560 -> 465 us, 22 views 1278 -> 1230 us (8 x 8 blocks: 499, 546, 1547); 8 x 8 blocks
+// halve a wave's serial work for launches with few tiles: 300k single view 140 -> 95 us (8 x 16: 166),
+// two small views 32 -> 24 us (41).  GA: the upstream adjoint has an alpha term (dL/dA); the fused
+// loss never has one.  S2: the loss has an adjoint for the second depth moment sum w z^2 (rendered
+// variance).
+template <int T, int PPT, int GRP, bool GA, bool S2>
 __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a) {
-    constexpr int NT = T * T / PPT;
-    // merge the waves' sums in LDS where that keeps the workgroup within 8 KB of LDS
-    constexpr bool MERGE = M <= 64 && NT > 64;
-    __shared__ SRec srec[M];
-    __shared__ float sacc[MERGE ? M * kGrad2d : 1];  // per LDS slot: the workgroup's ten sums
-    __shared__ uint32_t sq[2][MERGE ? M : 1];        // the pairs of this batch and the previous
-    __shared__ uint32_t smax;
-    __shared__ float sred[NT / 64];
-    // per wave, one bit per LDS slot of the batch: the record's footprint box meets the wave's
-    // block (read into scalar registers once per batch, so an entry's skip test costs no
-    // vector instruction and waits on no LDS read)
-    constexpr int kWords = (M + 63) / 64;
-    __shared__ unsigned long long smask[NT / 64][kWords];
+    constexpr int NW = T * T / PPT / 64, COLS = T / 8;
+    __shared__ Rows<GRP> rows[NW];
+    __shared__ uint32_t rpair[NW][kChunk + GRP];
+    __shared__ float sred[NW];
     const uint32_t wt = a.work[blockIdx.x];
     if (wt == kNoTile) return;  // padding of a shorter XCD list (whole workgroup)
     const int tile = (int)wt;
     const TileCoord tc = tile_coord(a.vt, tile);
     const uint32_t start = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile]);
-    const int tid = threadIdx.x;
     const int lane = __lane_id();
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Rows<GRP>& my = rows[wave];
+    uint32_t* const mypair = rpair[wave];
     const float amin = a.st.alpha_min;
 
     // U = T_final gC.bg + sum over later contributors j of w_j (gC.c_j + gD z_j + gA)
-    float cx[PPT], cy[PPT], Tr[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT], gA[PPT], gM[PPT], U[PPT];
+    const int bx = tc.px0 + (wave % COLS) * 8, by = tc.py0 + (wave / COLS) * 8 * PPT;
+    const int px = bx + (lane & 7), py = by + (lane >> 3);
+    const float cx = (float)px + 0.5f;
+    float cy[PPT], Tr[PPT], gC0[PPT], gC1[PPT], gC2[PPT], gD[PPT], gX[PPT], U[PPT];
     uint32_t last[PPT];
     float loss_part = 0.f;
-    uint32_t mylast = 0;
+    uint32_t wlast = 0;
     const long long plane = (long long)tc.W * tc.H;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        int lx, ly;
-        pixel_of<T, PPT, true>(tid, k, lx, ly);
-        const int px = tc.px0 + lx, py = tc.py0 + ly;
-        cx[k] = (float)px + 0.5f;
-        cy[k] = (float)py + 0.5f;
-        gC0[k] = gC1[k] = gC2[k] = gD[k] = gA[k] = gM[k] = 0.f;
+        const int y = py + 8 * k;
+        cy[k] = (float)y + 0.5f;
+        gC0[k] = gC1[k] = gC2[k] = gD[k] = gX[k] = 0.f;  // gX: gA or the second moment's adjoint
         Tr[k] = 1.f;
         last[k] = 0;
         U[k] = 0.f;
-        if (px < tc.W && py < tc.H) {
-            const long long p = (long long)py * tc.W + px;
+        if (px < tc.W && y < tc.H) {
+            const long long p = (long long)y * tc.W + px;
             const long long gp = tc.pix0 + p;
             Tr[k] = a.t_final[gp];
             last[k] = a.last[gp];
@@ -385,7 +494,7 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                     gC2[k] += g[2 * plane + p];
                 }
                 if (a.d_depth) gD[k] = a.d_depth[gp];
-                if (S2) gM[k] = a.d_depth2[gp];
+                if (S2) gX[k] = a.d_depth2[gp];
             } else {
                 if (a.d_rgb) {
                     const float* g = a.d_rgb + 3 * tc.pix0;
@@ -394,161 +503,120 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                     gC2[k] = g[2 * plane + p];
                 }
                 if (a.d_depth) gD[k] = a.d_depth[gp];
-                if (GA) gA[k] = a.d_alpha[gp];
+                if (GA) gX[k] = a.d_alpha[gp];
             }
             U[k] = Tr[k] * (gC0[k] * a.st.bg0 + gC1[k] * a.st.bg1 + gC2[k] * a.st.bg2);
-            mylast = max(mylast, last[k]);
+            wlast = max(wlast, last[k]);
         }
     }
     if (a.loss_mode) {
-        // block sum of the L1 partials (deterministic order)
+        // tile sum of the L1 partials (deterministic order)
         float s = wave_sum(loss_part);
-        if (lane == 0) sred[tid >> 6] = s;
+        if (NW > 1) {
+            if (lane == 0) sred[wave] = s;
+            __syncthreads();
+            s = 0.f;
+            for (int w = 0; w < NW; ++w) s += sred[w];
+        }
+        if (threadIdx.x == 0) a.loss_partials[tile] = s;
     }
-    if (tid == 0) smax = 0;
-    if (MERGE)
-        for (int l = tid; l < M * kGrad2d; l += NT) sacc[l] = 0.f;
-    __syncthreads();
-    atomicMax(&smax, mylast);
-    if (a.loss_mode && tid == 0) {
-        float s = 0.f;
-        for (int w = 0; w < NT / 64; ++w) s += sred[w];
-        a.loss_partials[tile] = s;
-    }
-    __syncthreads();
-    const uint32_t maxlast = smax;
-    // wave-uniform bound: entries at or past every lane's last contributor are skipped
-    uint32_t wlast = mylast;
+    // entries at or past every lane's last contributor are not visited
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) wlast = max(wlast, (uint32_t)__shfl_xor((int)wlast, o, 64));
     const int wl = (int)__builtin_amdgcn_readfirstlane(wlast);
 
+    prio_by_length(wl);
     const float amax = __builtin_canonicalizef(a.st.alpha_max);
-    // lane L ends the reduction holding slot (L >> 2) & 15; value v of the ten sums sits in
-    // slot kSlot[v % 5] + 8 (v / 5), see wave_transpose_sum10
-    const int slot = (lane >> 2) & 15, sl = slot & 7;
-    const bool red_lane = (lane & 3) == 0 && sl != 3 && sl < 6;
-    const int red_val = (sl < 3 ? sl : sl - 1) + 5 * (slot >> 3);
+    const float inv_amin = 1.f / amin;
+    const float X0 = (float)bx + 0.5f, Y0 = (float)by + 0.5f;
+    // odd waves add their six sums of p to a second set of slots, see kGrad2d
+    int red_val = column_sum_of(lane);
+    if ((wave & 1) && red_val >= 0 && red_val < kGrad2dSplit) red_val += kGrad2d;
 
-    // the batch's totals into the pairs' rows, one global atomic per (Gaussian, non-zero sum);
-    // the accumulator is left zero for the next batch
-    auto flush = [&](int n, const uint32_t* q) {
-        for (int l = tid; l < n * kGrad2d; l += NT) {
-            const float x = sacc[l];
-            if (x != 0.f) {
-                const int e = l / kGrad2d;
-                atomicAdd(a.grad2d + (long long)q[e] * kGrad2dStride + (l - e * kGrad2d), x);
-                sacc[l] = 0.f;
-            }
-        }
-    };
-    int prev_n = 0, buf = 0;
-    for (int hi = (int)maxlast; hi > 0; hi -= M, buf ^= 1) {
-        const int lo = hi - M > 0 ? hi - M : 0;
-        if (MERGE) flush(prev_n, sq[buf ^ 1]);  // the previous batch, while this one is staged
-        for (int base = 0; base < hi - lo; base += NT) {  // workgroup-uniform trip count
-            const int l = base + tid;
-            uint32_t m = 0;
-            if (l < hi - lo) {
-                const uint32_t q = a.tile_pairs[start + lo + l];
-                m = stage_record<T, PPT, true>(a.records, q, amin, tc.W, tc.H, tc.px0, tc.py0, srec[l], a.grad2d);
-                if (MERGE) sq[buf][l] = q;
-            }
-            const int l0 = base + 64 * wave;  // this wave's first slot
-            if (l0 < M) {
+    for (int hi = wl; hi > 0; hi -= kChunk) {  // the chunk's entries back to front
+        const int e = hi - 1 - lane;
+        const uint32_t q = a.tile_pairs[start + (e >= 0 ? e : 0)];
+        const Rec r = load_rec(a.records, q);
+        const bool in = e >= 0 && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, Y0, 7.f, 8.f * PPT - 1.f);
+        if (in) mypair[rank_in(__builtin_amdgcn_ballot_w64(in))] = q;
+        bool slow;
+        const int n = my.pack(r, in, (uint32_t)e, amax, slow);
+        auto run = [&](auto tests) {
+            constexpr bool TESTS = decltype(tests)::value;
+            for (int g = 0; g < n; g += GRP) {
+                float4 r0[GRP], rc[GRP];
+                float2 r1[GRP];
+                uint32_t j[GRP];
 #pragma unroll
-                for (int w = 0; w < NT / 64; ++w) {
-                    const unsigned long long bits = __ballot((m >> w) & 1u);
-                    if (lane == 0) smask[w][l0 >> 6] = bits;
+                for (int i = 0; i < GRP; ++i) {
+                    r0[i] = my.g[g + i];
+                    r1[i] = my.co[g + i];
+                    rc[i] = my.col[g + i];
+                    j[i] = my.pos[g + i];
+                }
+                float araw[GRP][PPT];
+                unsigned long long km[GRP][PPT];  // lanes that keep the pair
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+                    const float dx = r0[i].x - cx;
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        const float p2 = exponent2(r0[i].z, r0[i].w, r1[i].x, dx, r0[i].y - cy[k]);
+                        araw[i][k] = r1[i].y * __builtin_amdgcn_exp2f(p2);
+                        km[i][k] = __builtin_amdgcn_uicmp(j[i], last[k], 36) &  // j < last
+                                   le_mask(amin, TESTS ? fminf(amax, araw[i][k]) : araw[i][k]);
+                        if (TESTS) km[i][k] &= le_mask(p2, 0.f);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < GRP; ++i) {
+                    if ((km[i][0] | km[i][PPT - 1]) == 0ull) continue;  // wave-uniform
+                    const float dx = r0[i].x - cx;
+                    const float z = rc[i].w, z2 = S2 ? z * z : 0.f;
+                    float h[PPT], c[4];
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) {
+                        // branch-free: a pixel that does not keep this Gaussian has alpha = 0, so its w
+                        // and h are 0 and its T and U stay as they are (and every quantity stays
+                        // finite: alpha <= alpha_max < 1)
+                        const float ak = lane_of(km[i][k]) ? (TESTS ? fminf(amax, araw[i][k]) : araw[i][k]) : 0.f;
+                        const float om = 1.f - ak;
+                        float rom = __builtin_amdgcn_rcpf(om);
+                        const float Tk = Tr[k] * rom;
+                        const float w = ak * Tk;
+                        float qv = gC0[k] * rc[i].x + gC1[k] * rc[i].y + gC2[k] * rc[i].z + gD[k] * z;
+                        if (GA) qv += gX[k];
+                        if (S2) qv += gX[k] * z2;
+                        const float ga = Tk * qv - U[k] * rom;  // dL/dalpha
+                        U[k] += w * qv;
+                        Tr[k] = Tk;
+                        // dL/dpower = alpha dL/dalpha (none where the alpha_max clamp is active)
+                        h[k] = TESTS && !(araw[i][k] <= amax) ? 0.f : ga * ak;
+                        // depth adjoint: d(w z)/dz = w, d(w z^2)/dz = 2 w z
+                        const float gz = S2 ? gD[k] + 2.f * z * gX[k] : gD[k];
+                        c[0] = k == 0 ? w * gC0[k] : c[0] + w * gC0[k];
+                        c[1] = k == 0 ? w * gC1[k] : c[1] + w * gC1[k];
+                        c[2] = k == 0 ? w * gC2[k] : c[2] + w * gC2[k];
+                        c[3] = k == 0 ? w * gz : c[3] + w * gz;
+                    }
+                    const float dy0 = r0[i].y - cy[0];
+                    float hs = h[0], hy = h[0] * dy0, hyy = hy * dy0;
+                    if (PPT == 2) {
+                        const float dy1 = r0[i].y - cy[PPT - 1], t = h[PPT - 1] * dy1;
+                        hs += h[PPT - 1];
+                        hy += t;
+                        hyy += t * dy1;
+                    }
+                    const float tot = wave_column_sums(hs, hy, hyy, c, dx);
+                    const uint32_t pair = mypair[g + i];
+                    if (red_val >= 0) atomicAdd(a.grad2d + red_val + (long long)pair * kGrad2dStride, tot);
                 }
             }
-        }
-        prev_n = hi - lo;
-        __syncthreads();
-        unsigned long long mw[kWords];
-#pragma unroll
-        for (int x = 0; x < kWords; ++x) {
-            const unsigned long long v = smask[wave][x];
-            mw[x] = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-                    (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-        }
-        const int jtop = min(hi, wl);  // wave-uniform
-        // entries in groups of four, back to front: the group's records are read at immediate
-        // offsets from the LDS address of its lowest entry, which moves once per group
-        auto entry = [&](const SRec& r, int j, int e) {
-            if (!((mw[e >> 6] >> (e & 63)) & 1ull)) return;  // wave-uniform
-            const float4 rm = r.m, r0 = r.g0, r1 = r.g1;
-            float* const row = MERGE ? nullptr : r.row;
-            use_record(rm, r0, r1);
-            const float z2 = S2 ? r.z2 : 0.f;
-            // wave-level pre-test on the exponent alone; the adjoint runs only if some lane
-            // passes (every lane that keeps this Gaussian passes: the floor sits a margin below
-            // the exact threshold; keeps are decided on alpha below, as in the forward)
-            float p2v[PPT];
-            bool pass[PPT];
-            bool anyp = false;
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                p2v[k] = power_of(r0, r1, r0.x - cx[k], r0.y - cy[k]);
-                pass[k] = (uint32_t)j < last[k] && p2v[k] <= 0.f && p2v[k] >= r1.w;
-                anyp |= pass[k];
-            }
-            if (__ballot(anyp) == 0ull) return;  // wave-uniform
-            float g[10];
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                const float dx = r0.x - cx[k], dy = r0.y - cy[k];
-                const float p2 = p2v[k];
-                const float G = __builtin_amdgcn_exp2f(p2);  // e^power
-                const float araw = r1.y * G;
-                const float alpha = fminf(amax, araw);
-                const bool keep = pass[k] && alpha >= amin;
-                // branch-free: a lane that does not keep this Gaussian runs the same steps
-                // with alpha = 0, so its w is 0 and its T and U stay as they are (and every
-                // quantity stays finite: alpha <= alpha_max < 1)
-                const float ak = keep ? alpha : 0.f;
-                const float rom = __builtin_amdgcn_rcpf(1.f - ak);
-                const float Tk = Tr[k] * rom;
-                const float w = ak * Tk;
-                float qv = gC0[k] * rm.y + gC1[k] * rm.z + gC2[k] * rm.w + gD[k] * r1.z;
-                if (GA) qv += gA[k];
-                if (S2) qv += gM[k] * z2;
-                const float ga = Tk * qv - U[k] * rom;  // dL/dalpha
-                U[k] += w * qv;
-                Tr[k] = Tk;
-                // through alpha = o e^power (no gradient where the alpha_max clamp is active):
-                // h = dL/do, and dL/dpower = h o, whose factor o the projection backward
-                // applies to the five pixel moments kept here (sum h dx, h dy, h dx^2, h dx dy,
-                // h dy^2); it turns them into the centre and conic adjoints
-                const float h = (keep && araw <= amax) ? ga * G : 0.f;
-                const float t1 = h * dx, t2 = h * dy;
-                // depth adjoint: d(w z)/dz = w, d(w z^2)/dz = 2 w z
-                const float gz = S2 ? gD[k] + 2.f * r1.z * gM[k] : gD[k];
-                const float c[10] = {t1, t2, t1 * dx, t1 * dy, t2 * dy, h,
-                                     w * gC0[k], w * gC1[k], w * gC2[k], w * gz};
-#pragma unroll
-                for (int s = 0; s < 10; ++s) g[s] = k == 0 ? c[s] : g[s] + c[s];
-            }
-            const float tot = wave_transpose_sum10(g);
-            if (MERGE) {
-                if (red_lane) atomicAdd(&sacc[e * kGrad2d + red_val], tot);
-            } else {
-                if (red_lane) atomicAdd(row + red_val, tot);
-            }
         };
-        const char* sbase = reinterpret_cast<const char*>(srec);
-        int j = jtop - 1;
-        int ofs = (j - 3 - lo) * (int)sizeof(SRec);  // byte offset of the group's lowest entry
-        in_vgpr(ofs);
-        for (; j >= lo + 3; j -= 4, ofs -= 4 * (int)sizeof(SRec)) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                entry(*reinterpret_cast<const SRec*>(sbase + ofs + (3 - g) * (int)sizeof(SRec)), j - g, j - g - lo);
-        }
-        for (; j >= lo; --j) entry(srec[j - lo], j, j - lo);
-        __syncthreads();
+        if (slow) run(std::true_type{});
+        else run(std::false_type{});
+        __builtin_amdgcn_wave_barrier();
     }
-    if (MERGE) flush(prev_n, sq[buf ^ 1]);
 }
 
 // The backward's clears in one launch, when the forward's own zeroing of these accumulators
@@ -629,40 +697,55 @@ int raster_shapes(int* tile, int* ppt, int* batch, int n_max) {
     return n;
 }
 
+// Whether a launch takes 8 x 16 blocks: from 8192 waves of them (256 CUs of 32 waves) the chip is
+// full with half the waves; an 8 x 8 tile has no 8 x 16 block.  Both sides measured at the kernels.
+static bool wide_blocks(const ViewTable& vt, int T) {
+    return T > 8 && (long long)vt.tile_base[vt.n_views] * (T * T / 128) >= 8192;
+}
+
+// `batch` and `ppt` only name a supported shape: how many entries and pixels a lane takes follows
+// from the number of blocks.
+static bool shape_supported(int T, int batch, int ppt) {
+#define X(t_, p_, m_) \
+    if (T == t_ && ppt == p_ && batch == m_) return true;
+    AGS_RASTER_CONFIGS(X)
+#undef X
+    return false;
+}
+
 int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_t s) {
     const int nb = raster_blocks(a.vt);
     if (nb <= 0) return 0;
-#define X(t_, p_, m_)                                                                              \
-    if (T == t_ && ppt == p_ && batch == m_) {                                                     \
-        if (a.depth_var)                                                                           \
-            hipLaunchKernelGGL((raster_fwd_kernel<t_, p_, m_, true>), dim3(nb), dim3(t_ * t_ / p_), 0, s, a); \
-        else                                                                                       \
-            hipLaunchKernelGGL((raster_fwd_kernel<t_, p_, m_, false>), dim3(nb), dim3(t_ * t_ / p_), 0, s, a); \
-        return 0;                                                                                  \
-    }
-    AGS_RASTER_CONFIGS(X)
-#undef X
-    return AGS_ERR_NOT_SUPPORTED;
+    if (!shape_supported(T, batch, ppt)) return AGS_ERR_NOT_SUPPORTED;
+    auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3(nb), dim3(threads), 0, s, a); };
+    const bool wide = wide_blocks(a.vt, T), var = a.depth_var != nullptr;
+    if (T == 8) var ? launch(raster_fwd_kernel<8, true>, 64) : launch(raster_fwd_kernel<8, false>, 64);
+    else if (T == 16 && wide) var ? launch(raster_fwd_wide_kernel<16, true>, 128) : launch(raster_fwd_wide_kernel<16, false>, 128);
+    else if (T == 16) var ? launch(raster_fwd_kernel<16, true>, 256) : launch(raster_fwd_kernel<16, false>, 256);
+    else if (wide) var ? launch(raster_fwd_wide_kernel<32, true>, 512) : launch(raster_fwd_wide_kernel<32, false>, 512);
+    else var ? launch(raster_fwd_kernel<32, true>, 1024) : launch(raster_fwd_kernel<32, false>, 1024);
+    return 0;
+}
+
+template <int T, int PPT, int GRP>
+static void bwd_variant(const RasterBwdArgs& a, int nb, hipStream_t s) {
+    const dim3 grid(nb), block(T * T / PPT);
+    if (!a.loss_mode && a.d_alpha) hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, true, false>), grid, block, 0, s, a);
+    else if (a.loss_mode && a.d_depth2) hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, false, false>), grid, block, 0, s, a);
 }
 
 int launch_raster_bwd(const RasterBwdArgs& a, int T, int batch, int ppt, hipStream_t s) {
     const int nb = raster_blocks(a.vt);
     if (nb <= 0) return 0;
-    const bool ga = !a.loss_mode && a.d_alpha != nullptr;
-    const bool m2 = a.loss_mode && a.d_depth2 != nullptr;
-#define X(t_, p_, m_)                                                                                      \
-    if (T == t_ && ppt == p_ && batch == m_) {                                                             \
-        if (ga)                                                                                            \
-            hipLaunchKernelGGL((raster_bwd_kernel<t_, p_, m_, true, false>), dim3(nb), dim3(t_ * t_ / p_), 0, s, a); \
-        else if (m2)                                                                                       \
-            hipLaunchKernelGGL((raster_bwd_kernel<t_, p_, m_, false, true>), dim3(nb), dim3(t_ * t_ / p_), 0, s, a); \
-        else                                                                                               \
-            hipLaunchKernelGGL((raster_bwd_kernel<t_, p_, m_, false, false>), dim3(nb), dim3(t_ * t_ / p_), 0, s, a); \
-        return 0;                                                                                          \
-    }
-    AGS_RASTER_CONFIGS(X)
-#undef X
-    return AGS_ERR_NOT_SUPPORTED;
+    if (!shape_supported(T, batch, ppt)) return AGS_ERR_NOT_SUPPORTED;
+    const bool wide = wide_blocks(a.vt, T);
+    if (T == 8) bwd_variant<8, 1, 4>(a, nb, s);
+    else if (T == 16 && wide) bwd_variant<16, 2, 2>(a, nb, s);
+    else if (T == 16) bwd_variant<16, 1, 4>(a, nb, s);
+    else if (wide) bwd_variant<32, 2, 2>(a, nb, s);
+    else bwd_variant<32, 1, 4>(a, nb, s);
+    return 0;
 }
 
 }  // namespace ags
