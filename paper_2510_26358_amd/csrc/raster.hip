@@ -174,9 +174,9 @@ struct Rows {
 // shapes.
 struct Scatter {
     float A = 0.f, m = 0.f, S = 0.f;
-    __device__ __forceinline__ void add(float w, float z) {
-#pragma clang fp contract(off)
-        A += w;
+    __device__ __forceinline__ void add(float alpha, float T, float z) {
+        const float w = alpha * T;
+        A = __builtin_fmaf(alpha, T, A);
         const float dz = z - m;
         m = __builtin_fmaf(dz, w * __builtin_amdgcn_rcpf(A), m);
         S = __builtin_fmaf(w * dz, z - m, S);
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
                     const float w = lane_of(go) ? al[i] * Tr : 0.f;
                     C = __builtin_amdgcn_mfma_f32_4x4x1f32(colv, w, C, 4, i, 0);
                     if (lane_of(go)) {
-                        if (S2) var.add(w, my.col[g + i].w);
+                        if (S2) var.add(al[i], Tr, my.col[g + i].w);
                         Tr = Tn;
                         lastc = row + i;
                     }
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a)
                             C1[k] = __builtin_fmaf(w, rc[i].y, C1[k]);
                             C2[k] = __builtin_fmaf(w, rc[i].z, C2[k]);
                             D[k] = __builtin_fmaf(w, rc[i].w, D[k]);
-                            if (S2) var[k].add(w, rc[i].w);
+                            if (S2) var[k].add(al[i][k], Tr[k], rc[i].w);
                             Tr[k] = Tn;
                             lastc[k] = row + i;
                         }
