@@ -94,8 +94,9 @@ __device__ __forceinline__ bool needs_tests(float A, float B, float C, float o, 
     return !(o <= amax && A < 0.f && C < 0.f && B * B < 3.9999f * (A * C));
 }
 
-// The base-2 exponent A' dx^2 + B' dx dy + C' dy^2 in one fixed order of roundings, so that the
-// forward and the backward decide on the same bits.
+// The base-2 exponent A' dx^2 + B' dx dy + C' dy^2 in one fixed order of roundings for both block shapes.
+// (The backward's two pixels a lane share A' dx instead, which rounds B' dx dy's product the other way
+// round: their alpha may differ from the forward's in its last bit.)
 __device__ __forceinline__ float exponent2(float A, float B, float C, float dx, float dy) {
     return __builtin_fmaf(dy, dy * C, dx * __builtin_fmaf(dx, A, dy * B));
 }
@@ -558,10 +559,13 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                 unsigned long long km[GRP][PPT];  // lanes that keep the pair
 #pragma unroll
                 for (int i = 0; i < GRP; ++i) {
-                    const float dx = r0[i].x - cx;
+                    const float dx = r0[i].x - cx, Adx = r0[i].z * dx;
 #pragma unroll
                     for (int k = 0; k < PPT; ++k) {
-                        const float p2 = exponent2(r0[i].z, r0[i].w, r1[i].x, dx, r0[i].y - cy[k]);
+                        const float dy = r0[i].y - cy[k];
+                        const float p2 =
+                            PPT == 1 ? exponent2(r0[i].z, r0[i].w, r1[i].x, dx, dy)
+                                     : __builtin_fmaf(dy, dy * r1[i].x, dx * __builtin_fmaf(r0[i].w, dy, Adx));
                         araw[i][k] = r1[i].y * __builtin_amdgcn_exp2f(p2);
                         km[i][k] = __builtin_amdgcn_uicmp(j[i], last[k], 36) &  // j < last
                                    le_mask(amin, TESTS ? fminf(amax, araw[i][k]) : araw[i][k]);
