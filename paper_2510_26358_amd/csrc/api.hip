@@ -60,7 +60,7 @@ struct Layout {
         s_ddepth, s_ddepth2, s_total;
     // fwd ws
     size_t f_pair_z, f_dkeys0, f_dkeys1, f_dvals0, f_dvals1, f_emit_off, f_block_first, f_tkeys0, f_tkeys1,
-        f_tvals1, f_hist, f_rowtot, f_block_sums, f_total;
+        f_tvals1, f_hist, f_rowtot, f_block_sums, f_tile_count, f_total;
     // bwd ws
     size_t b_dssim, b_partials, b_pose_part, b_vis, b_total;
     long long n_partials, n_ssim;
@@ -165,6 +165,8 @@ int build_layout(const ags_config* cfg, const ags_views* views, int n, long long
     L.f_hist = o; o = align_up(o + (size_t)sort_hist_entries(gmax) * 4);
     L.f_rowtot = o; o = align_up(o + (size_t)sort_rowtot_entries() * 4);
     L.f_block_sums = o; o = align_up(o + (size_t)sb * 4);
+    L.f_tile_count = o;
+    if (per_tile_sort(vt, L.Q, L.cap)) o = align_up(o + 2 * (size_t)kTileCounts * L.n_tiles * 4);
     L.f_total = o;
     o = 0;
     L.n_ssim = ssim_blocks(vt);
@@ -234,6 +236,7 @@ BinArgs bin_args(const Layout& L, void* saved, void* ws) {
     a.depth_vals[1] = at<uint32_t>(ws, L.f_dvals1);
     a.emit_off = at<uint32_t>(ws, L.f_emit_off);
     a.block_first = at<uint32_t>(ws, L.f_block_first);
+    a.tile_count = at<uint32_t>(ws, L.f_tile_count);
     a.tile_keys[0] = at<uint32_t>(ws, L.f_tkeys0);
     a.tile_keys[1] = at<uint32_t>(ws, L.f_tkeys1);
     a.tile_vals[0] = at<uint32_t>(saved, L.s_tile_pairs);

@@ -8,7 +8,8 @@
 // depth-sorted once (V << K items, 32-bit keys) and their intersections are emitted in
 // that order; a stable sort on the tile id alone then yields exactly the same order
 // (LSD radix passes are stable).  Bytes moved: 4 passes x V + ceil(tile_bits / 8) passes
-// x K instead of 6 passes x K with 12-byte records.
+// x K instead of 6 passes x K with 12-byte records.  Launches with few intersections sort
+// each tile's list by itself instead (see per_tile_sort): fewer launches, the same lists.
 #include "common.h"
 
 namespace ags {
@@ -23,13 +24,22 @@ namespace ags {
 // alpha >= alpha_min ellipse does not reach (tile_reached) gets the key n_tiles, which the
 // tile sort's first pass drops.  Balanced however unequal the footprints are, and the
 // writes are coalesced.
+//
+// RANK (the pairs are in pair order): the kernel also counts each tile's intersections and writes each
+// one's rank in that count to tile_rank.  There are kTileCounts counts [kTileCounts][n_tiles], cleared
+// before, of which workgroup g uses number g % kTileCounts: consecutive workgroups run on the eight
+// XCDs in turn, so a counter's cache line stays in one XCD's L2 instead of moving between them for
+// every atomic (one 960 x 600 view over 300k Gaussians, one count: 66 us, eight 29, sixteen 20; without
+// counts 8).
 constexpr int kEmitThreads = 256;
 
+template <bool RANK>
 __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const float* records,
                                                             const uint32_t* depth_vals, const uint32_t* emit_off,
                                                             const uint32_t* block_first, const uint32_t* counters,
                                                             long long capacity, uint32_t* tile_keys,
-                                                            uint32_t* tile_vals, uint32_t* ranges) {
+                                                            uint32_t* tile_vals, uint32_t* tile_rank,
+                                                            uint32_t* tile_count, uint32_t* ranges) {
     constexpr int S = kEmitSlots, PT = S / kEmitThreads;
     __shared__ uint32_t s_off[S];
     __shared__ uint32_t s_own[S];                     // slot -> local pair index
@@ -41,9 +51,11 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const 
     const long long k0 = (long long)blockIdx.x * S;
     const uint32_t n_tiles = (uint32_t)vt.tile_base[vt.n_views];
     // every tile's range starts empty; ranges_kernel later sets the non-empty ones
-    for (long long e = (long long)blockIdx.x * kEmitThreads + threadIdx.x; e < 2LL * n_tiles;
-         e += (long long)gridDim.x * kEmitThreads)
-        ranges[e] = 0u;
+    if (!RANK) {
+        for (long long e = (long long)blockIdx.x * kEmitThreads + threadIdx.x; e < 2LL * n_tiles;
+             e += (long long)gridDim.x * kEmitThreads)
+            ranges[e] = 0u;
+    }
     long long keff = counters[CNT_KEFF];
     if (keff > capacity) keff = capacity;
     const long long nv = counters[CNT_V];
@@ -135,8 +147,10 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const 
         const float2 e2 = s_ell2[lo];
         const bool hit = tile_reached(e.x, e.y, e.z, e.w, e2.x, e2.y, tx, ty, vt.tile, (int)(wh & 0xFFFFu),
                                       (int)(wh >> 16));
-        tile_keys[k] = hit ? s_first[lo] + row * (wp >> 16) + col : n_tiles;
+        const uint32_t tile = hit ? s_first[lo] + row * (wp >> 16) + col : n_tiles;
+        tile_keys[k] = tile;
         tile_vals[k] = s_q[lo];
+        if (RANK && hit) tile_rank[k] = atomicAdd(tile_count + (size_t)(blockIdx.x % kTileCounts) * n_tiles + tile, 1u);
     }
 }
 
@@ -177,10 +191,10 @@ __global__ __launch_bounds__(256) void ranges_kernel(const uint32_t* keys, const
 // slot of its bucket (the order inside a bucket is that of the claims; any order gives the
 // same image).
 constexpr int kWorkThreads = 1024, kWorkBuckets = 64;
-__global__ __launch_bounds__(kWorkThreads) void work_list_kernel(const uint32_t* ranges, int n_tiles, int n_slots,
-                                                                 uint32_t* work) {
+template <typename Len>
+__device__ __forceinline__ void work_list_of(int x, int n_tiles, int n_slots, uint32_t* work, Len length) {
     __shared__ uint32_t cnt[kWorkBuckets];
-    const int t = threadIdx.x, x = blockIdx.x;
+    const int t = threadIdx.x;
     const int per = n_slots / 8;  // slots of one XCD list (a whole number of strips)
     if (t < kWorkBuckets) cnt[t] = 0;
     for (int k = t; k < per; k += kWorkThreads) work[8 * k + x] = kNoTile;
@@ -188,8 +202,7 @@ __global__ __launch_bounds__(kWorkThreads) void work_list_kernel(const uint32_t*
     // i-th tile of XCD x: strip x + 8 (i / kWorkStrip), position i % kWorkStrip in it
     auto tile_of = [&](int i) { return (x + 8 * (i / kWorkStrip)) * kWorkStrip + i % kWorkStrip; };
     auto bucket = [&](int tile) {
-        const uint32_t len = ranges[2 * tile + 1] - ranges[2 * tile];
-        const int b = (int)(4.f * log2f((float)len + 1.f));
+        const int b = (int)(4.f * log2f((float)length(tile) + 1.f));
         return b < kWorkBuckets - 1 ? b : kWorkBuckets - 1;
     };
     for (int i = t; i < per; i += kWorkThreads) {
@@ -209,6 +222,334 @@ __global__ __launch_bounds__(kWorkThreads) void work_list_kernel(const uint32_t*
     for (int i = t; i < per; i += kWorkThreads) {
         const int tile = tile_of(i);
         if (tile < n_tiles) work[8 * atomicAdd(&cnt[bucket(tile)], 1u) + x] = (uint32_t)tile;
+    }
+}
+
+__global__ __launch_bounds__(kWorkThreads) void work_list_kernel(const uint32_t* ranges, int n_tiles, int n_slots,
+                                                                 uint32_t* work) {
+    work_list_of((int)blockIdx.x, n_tiles, n_slots, work,
+                 [&](int tile) { return ranges[2 * tile + 1] - ranges[2 * tile]; });
+}
+
+// ------------------------------------------------------------------------- per-tile sort
+//
+// The other way to the same lists, for launches whose lists are short: the pairs are emitted in pair
+// order, each intersection takes its place in its tile by a counter, and one workgroup a tile sorts the
+// tile's list by (depth bits, pair id).  Six launches instead of 23, of which none reads more than a few
+// megabytes: a launch costs about 4.5 us however little it does, so the two radix sorts cost about
+// 170 us of a 300k-Gaussian single view's step and 60 us of one over 4k.
+//
+// pair_reduce_kernel and pair_apply_kernel compact the visible pairs in pair order and scan their tile
+// counts: out[j] = first slot of the j-th visible pair, which[j] = that pair, block_first as for
+// emit_apply_kernel, and the counters.  sums: [gridDim][2] (slots, visible pairs) of each block.
+constexpr int kPairThreads = 256, kPairItems = 8, kPairBlock = kPairThreads * kPairItems;
+
+__device__ __forceinline__ uint2 wave_inclusive2(uint2 v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)v.x, o, 64), y = (uint32_t)__shfl_up((int)v.y, o, 64);
+        if (lane >= o) {
+            v.x += x;
+            v.y += y;
+        }
+    }
+    return v;
+}
+
+// Inclusive scan over the workgroup; `total` of all threads.
+__device__ __forceinline__ uint2 block_inclusive2(uint2 v, uint2* wave_tot, uint2& total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    v = wave_inclusive2(v, lane);
+    if (lane == 63) wave_tot[w] = v;
+    __syncthreads();
+    total = make_uint2(0u, 0u);
+#pragma unroll
+    for (int x = 0; x < kPairThreads / 64; ++x) {
+        const uint2 y = wave_tot[x];
+        if (x < w) {
+            v.x += y.x;
+            v.y += y.y;
+        }
+        total.x += y.x;
+        total.y += y.y;
+    }
+    __syncthreads();
+    return v;
+}
+
+__device__ __forceinline__ void load_counts(const uint32_t* pair_count, long long n, long long i0,
+                                            uint32_t (&c)[kPairItems]) {
+    if (i0 + kPairItems <= n) {  // i0 is a multiple of 8: 16-byte aligned
+        const uint4 p = reinterpret_cast<const uint4*>(pair_count + i0)[0];
+        const uint4 q = reinterpret_cast<const uint4*>(pair_count + i0)[1];
+        c[0] = p.x; c[1] = p.y; c[2] = p.z; c[3] = p.w;
+        c[4] = q.x; c[5] = q.y; c[6] = q.z; c[7] = q.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPairItems; ++k) c[k] = i0 + k < n ? pair_count[i0 + k] : 0u;
+    }
+}
+
+// Also clears the tile counts.
+__global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_t* pair_count, long long n,
+                                                                   uint2* sums, uint32_t* tile_count, long long n_counts) {
+    __shared__ uint2 wave_tot[kPairThreads / 64];
+    const long long g = (long long)blockIdx.x * kPairThreads + threadIdx.x;
+    for (long long e = g; e < n_counts; e += (long long)gridDim.x * kPairThreads) tile_count[e] = 0u;
+    uint32_t c[kPairItems];
+    load_counts(pair_count, n, g * kPairItems, c);
+    uint2 v = make_uint2(0u, 0u), total;
+#pragma unroll
+    for (int k = 0; k < kPairItems; ++k) {
+        v.x += c[k];
+        v.y += c[k] ? 1u : 0u;
+    }
+    block_inclusive2(v, wave_tot, total);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t* pair_count, long long n,
+                                                                  const uint2* sums, long long capacity,
+                                                                  uint32_t* which, uint32_t* out,
+                                                                  uint32_t* block_first, uint32_t* counters) {
+    __shared__ uint2 wave_tot[kPairThreads / 64];
+    uint2 pre = make_uint2(0u, 0u), before, total;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += kPairThreads) {
+        pre.x += sums[b].x;
+        pre.y += sums[b].y;
+    }
+    block_inclusive2(pre, wave_tot, before);
+    const long long i0 = ((long long)blockIdx.x * kPairThreads + threadIdx.x) * kPairItems;
+    uint32_t c[kPairItems];
+    load_counts(pair_count, n, i0, c);
+    uint2 v = make_uint2(0u, 0u);
+#pragma unroll
+    for (int k = 0; k < kPairItems; ++k) {
+        v.x += c[k];
+        v.y += c[k] ? 1u : 0u;
+    }
+    const uint2 incl = block_inclusive2(v, wave_tot, total);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        const uint32_t K = before.x + total.x;
+        const bool over = (long long)K > capacity;
+        counters[CNT_K] = K;
+        counters[CNT_V] = before.y + total.y;
+        counters[CNT_OVERFLOW] = over ? 1u : 0u;
+        counters[CNT_KEFF] = over ? (uint32_t)capacity : K;
+    }
+    uint32_t run = before.x + incl.x - v.x, j = before.y + incl.y - v.y;
+#pragma unroll
+    for (int k = 0; k < kPairItems; ++k) {
+        if (!c[k]) continue;
+        which[j] = (uint32_t)(i0 + k);
+        out[j] = run;
+        const long long e = (long long)run + c[k];
+        for (long long m = ((long long)run + kEmitSlots - 1) / kEmitSlots * kEmitSlots; m < e && m < capacity;
+             m += kEmitSlots)
+            block_first[m / kEmitSlots] = j;
+        run += c[k];
+        ++j;
+    }
+}
+
+// The tile counts to the tiles' ranges, the first place of each (tile, count) and the list total
+// (workgroups 8 and up, 1024 tiles each, adding up the tiles before their own), and the raster work order
+// (workgroups 0..7, from the counts alone, so that nobody waits).
+__global__ __launch_bounds__(kWorkThreads) void tile_scan_kernel(const uint32_t* tile_count, uint32_t* tile_base,
+                                                                 uint32_t* ranges, int n_tiles, int n_slots,
+                                                                 uint32_t* work, uint32_t* counters) {
+    auto length = [&](int tile) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int x = 0; x < kTileCounts; ++x) n += tile_count[(size_t)x * n_tiles + tile];
+        return n;
+    };
+    if (blockIdx.x < 8) {
+        work_list_of((int)blockIdx.x, n_tiles, n_slots, work, length);
+        return;
+    }
+    __shared__ uint32_t wave_tot[2][kWorkThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int first = ((int)blockIdx.x - 8) * kWorkThreads, tile = first + t;
+    uint32_t before = 0;
+    for (int i = t; i < first; i += kWorkThreads) before += length(i);
+    uint32_t c[kTileCounts], sum = 0;
+#pragma unroll
+    for (int x = 0; x < kTileCounts; ++x) {
+        c[x] = tile < n_tiles ? tile_count[(size_t)x * n_tiles + tile] : 0u;
+        sum += c[x];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
+        if (lane >= o) incl += y;
+        before += (uint32_t)__shfl_xor((int)before, o, 64);
+    }
+    if (lane == 63) {
+        wave_tot[0][w] = incl;
+        wave_tot[1][w] = before;
+    }
+    __syncthreads();
+    uint32_t run = incl - sum, total = 0;
+#pragma unroll
+    for (int x = 0; x < kWorkThreads / 64; ++x) {
+        run += (x < w ? wave_tot[0][x] : 0u) + wave_tot[1][x];
+        total += wave_tot[0][x] + wave_tot[1][x];
+    }
+    if (blockIdx.x == gridDim.x - 1 && t == 0) counters[CNT_LIVE] = total;
+    if (tile >= n_tiles) return;
+    reinterpret_cast<uint2*>(ranges)[tile] = sum ? make_uint2(run, run + sum) : make_uint2(0u, 0u);
+#pragma unroll
+    for (int x = 0; x < kTileCounts; ++x) {
+        tile_base[(size_t)x * n_tiles + tile] = run;
+        run += c[x];
+    }
+}
+
+// Each intersection's pair id to its place in its tile.
+constexpr int kPlaceItems = kEmitSlots / 256;
+__global__ __launch_bounds__(256) void place_kernel(const uint32_t* tile_keys, const uint32_t* tile_vals,
+                                                    const uint32_t* tile_rank, const uint32_t* tile_base,
+                                                    const uint32_t* counters, long long capacity, uint32_t n_tiles,
+                                                    uint32_t* out) {
+    long long n = counters[CNT_KEFF];
+    if (n > capacity) n = capacity;
+    const long long k0 = (long long)blockIdx.x * kEmitSlots + threadIdx.x;  // the slots of one emission workgroup
+    const uint32_t* base = tile_base + (size_t)(blockIdx.x % kTileCounts) * n_tiles;
+    uint32_t t[kPlaceItems], q[kPlaceItems], r[kPlaceItems];
+#pragma unroll
+    for (int j = 0; j < kPlaceItems; ++j) {
+        const long long k = k0 + 256 * j;
+        t[j] = k < n ? tile_keys[k] : n_tiles;
+        q[j] = k < n ? tile_vals[k] : 0u;
+        r[j] = k < n ? tile_rank[k] : 0u;  // not written where the tile was rejected, and not used
+    }
+#pragma unroll
+    for (int j = 0; j < kPlaceItems; ++j)
+        if (t[j] < n_tiles) out[base[t[j]] + r[j]] = q[j];
+}
+
+// One workgroup sorts a tile's list by (depth bits, pair id), a strict order: runs of 64 by each
+// element's rank among its run, then merges in which an element's place is its index in its own run plus
+// its rank in the other (a binary search), all in LDS up to kTileSortLds entries.  A longer list is
+// sorted in pieces of that length, which are then merged through global memory, between the pairs of
+// arrays (za, qa) and (zb, qb), ending in (zb, qb).  On entry the list is in qa; on exit its ids are in qb
+// and the tile's id in zb.  The workgroups follow the raster work order, the longest lists first.
+constexpr int kTileSortThreads = 256;
+constexpr int kTileSortLds = 1024;  // two buffers of 8 KB: eight workgroups on a CU
+constexpr int kMergeItems = 4;  // searches a thread runs side by side
+
+// Orders the wave's own LDS accesses (which complete in order) for the compiler.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One level of merges of runs of R (a power of two) of n elements: element i to place(i's new place).
+template <typename Load, typename Place>
+__device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, Place place) {
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kMergeItems * kTileSortThreads) {
+        unsigned long long key[kMergeItems];
+        uint32_t lo[kMergeItems], ps[kMergeItems], pl[kMergeItems];  // the other run: start, length
+#pragma unroll
+        for (int k = 0; k < kMergeItems; ++k) {
+            const uint32_t i = i0 + k * kTileSortThreads;
+            const bool in = i < n;
+            key[k] = in ? load(i) : 0ull;
+            ps[k] = (i ^ R) & ~(R - 1);
+            pl[k] = in && ps[k] < n ? (n - ps[k] < R ? n - ps[k] : R) : 0u;
+            lo[k] = 0;
+        }
+        for (uint32_t step = R; step > 0; step >>= 1) {
+#pragma unroll
+            for (int k = 0; k < kMergeItems; ++k) {
+                const uint32_t m = lo[k] + step;
+                if (m <= pl[k] && load(ps[k] + m - 1) < key[k]) lo[k] = m;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kMergeItems; ++k) {
+            const uint32_t i = i0 + k * kTileSortThreads;
+            if (i < n) place((i & ~(2 * R - 1)) + (i & (R - 1)) + lo[k], key[k]);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint32_t* pair_z, const uint32_t* ranges,
+                                                                     const uint32_t* work, uint32_t* za,
+                                                                     uint32_t* qa, uint32_t* zb, uint32_t* qb) {
+    using u64 = unsigned long long;
+    __shared__ __align__(16) u64 buf[2][kTileSortLds];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const uint32_t tile = work[blockIdx.x];
+    if (tile == kNoTile) return;
+    const uint2 se = reinterpret_cast<const uint2*>(ranges)[tile];
+    const uint32_t n = se.y - se.x, s = se.x;
+    int levels = 0;  // merges through global memory
+    while (((uint32_t)kTileSortLds << levels) < n) ++levels;
+    for (uint32_t c0 = 0; c0 < n; c0 += kTileSortLds) {
+        const uint32_t len = n - c0 < (uint32_t)kTileSortLds ? n - c0 : kTileSortLds;
+        for (uint32_t i = t; i - lane < len; i += kTileSortThreads) {  // wave-uniform
+            // the last run's fillers are distinct and above every key
+            const uint32_t q = i < len ? qa[s + c0 + i] : i;
+            const uint32_t z = i < len ? pair_z[q] : 0xFFFFFFC0u + (uint32_t)lane;
+            const u64 key = ((u64)z << 32) | q;
+            // ranks by the depth bits alone, four to an LDS read; lanes of equal depth find another's
+            // entry in their place, and then the run is ranked by (depth, id)
+            u64* const run = buf[0] + (i - lane);
+            uint32_t* const rz = reinterpret_cast<uint32_t*>(run);
+            rz[lane] = z;
+            wave_sync();
+            int rank = 0;
+#pragma unroll 4
+            for (int j = 0; j < 16; ++j) {
+                const uint4 v = reinterpret_cast<const uint4*>(rz)[j];
+                rank += (v.x < z ? 1 : 0) + (v.y < z ? 1 : 0) + (v.z < z ? 1 : 0) + (v.w < z ? 1 : 0);
+            }
+            wave_sync();
+            run[rank] = key;
+            wave_sync();
+            if (__builtin_amdgcn_ballot_w64(run[rank] != key) != 0ull) {
+                wave_sync();
+                run[lane] = key;
+                wave_sync();
+                rank = 0;
+                for (int j = 0; j < 64; ++j) rank += run[j] < key ? 1 : 0;
+                wave_sync();
+                run[rank] = key;
+            }
+        }
+        __syncthreads();
+        int cur = 0;
+        for (uint32_t R = 64; R < len; R <<= 1, cur ^= 1) {
+            const u64* const in = buf[cur];
+            u64* const out = buf[cur ^ 1];
+            merge_level((len + 63) & ~63u, R, [&](uint32_t i) { return in[i]; },
+                        [&](uint32_t p, u64 key) { out[p] = key; });
+            __syncthreads();
+        }
+        uint32_t* const zo = levels & 1 ? za : zb;
+        uint32_t* const qo = levels & 1 ? qa : qb;
+        for (uint32_t i = t; i < len; i += kTileSortThreads) {
+            const u64 v = buf[cur][i];
+            zo[s + c0 + i] = levels ? (uint32_t)(v >> 32) : tile;
+            qo[s + c0 + i] = (uint32_t)v;
+        }
+        __syncthreads();
+    }
+    for (int l = levels; l > 0; --l) {  // from (za, qa) when l is odd
+        const uint32_t* const zi = (l & 1 ? za : zb) + s;
+        const uint32_t* const qi = (l & 1 ? qa : qb) + s;
+        uint32_t* const zo = (l & 1 ? zb : za) + s;
+        uint32_t* const qo = (l & 1 ? qb : qa) + s;
+        merge_level(n, (uint32_t)kTileSortLds << (levels - l),
+                    [&](uint32_t i) { return ((u64)zi[i] << 32) | qi[i]; },
+                    [&](uint32_t p, u64 key) {
+                        zo[p] = l == 1 ? tile : (uint32_t)(key >> 32);
+                        qo[p] = (uint32_t)key;
+                    });
+        __syncthreads();
     }
 }
 
@@ -238,7 +579,54 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
                        0, s, vt, records, valid, n_pairs, pair_count, pair_z);
 }
 
+// Which way a launch takes: the lists sorted tile by tile, or two radix sorts over all.  Tile by tile
+// is six launches (about 4.5 us each however little they do) against 23, but its atomics, scattered
+// places and merges cost more per intersection.  Binning of one 300k-Gaussian view (0.5M
+// intersections) 190 us by radix sorts, 67 tile by tile; three views over 600k (2.4M) 208 and 174; four
+// over 1M (7.5M) 304 and 378.  And one workgroup sorts a list, which beyond a few thousand entries takes
+// longer than all the radix passes (a piece of 1024 about 7 us, a merge level of 4096 about 30): no list can
+// be longer than its view's Gaussian range, or the capacity leaves at most 512 entries a tile on average.
+constexpr long long kTileSortCapacity = 1ll << 22, kTileSortLongest = 4096, kTileSortMean = 512;
+bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity) {
+    const long long n_tiles = vt.tile_base[vt.n_views];
+    if (n_pairs <= 0 || n_tiles <= 0 || capacity <= 0 || capacity > kTileSortCapacity) return false;
+    long long longest = 0;
+    for (int b = 0; b < vt.n_views; ++b) {
+        const long long n = vt.g_end[b] - vt.g_begin[b];
+        longest = n > longest ? n : longest;
+    }
+    return longest <= kTileSortLongest || capacity <= kTileSortLongest || capacity <= kTileSortMean * n_tiles;
+}
+
+static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
+    const int n_tiles = a.vt.tile_base[a.vt.n_views];
+    const unsigned pgrid = (unsigned)((a.n_pairs + kPairBlock - 1) / kPairBlock);
+    uint2* sums = reinterpret_cast<uint2*>(a.depth_keys[0]);
+    uint32_t* const count = a.tile_count;
+    uint32_t* const base = a.tile_count + (size_t)kTileCounts * n_tiles;
+    hipLaunchKernelGGL(pair_reduce_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, a.n_pairs, sums,
+                       count, (long long)kTileCounts * n_tiles);
+    hipLaunchKernelGGL(pair_apply_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, a.n_pairs, sums,
+                       a.capacity, a.depth_vals[0], a.emit_off, a.block_first, a.counters);
+    const unsigned egrid = (unsigned)((a.capacity + kEmitSlots - 1) / kEmitSlots);
+    uint32_t* const tk = a.tile_keys[0];
+    uint32_t* const tr = a.tile_keys[1];
+    uint32_t* const tv = a.final_vals;
+    uint32_t* const list = a.final_vals == a.tile_vals[0] ? a.tile_vals[1] : a.tile_vals[0];
+    hipLaunchKernelGGL(emit_kernel<true>, dim3(egrid), dim3(kEmitThreads), 0, s, a.vt, a.records, a.depth_vals[0],
+                       a.emit_off, a.block_first, a.counters, a.capacity, tk, tv, tr, count, a.ranges);
+    const unsigned tgrid = 8 + (unsigned)((n_tiles + kWorkThreads - 1) / kWorkThreads);
+    hipLaunchKernelGGL(tile_scan_kernel, dim3(tgrid), dim3(kWorkThreads), 0, s, count, base, a.ranges, n_tiles,
+                       raster_blocks(a.vt), a.work, a.counters);
+    hipLaunchKernelGGL(place_kernel, dim3(egrid), dim3(256), 0, s, tk, tv, tr, base, a.counters, a.capacity,
+                       (uint32_t)n_tiles, list);
+    hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)raster_blocks(a.vt)), dim3(kTileSortThreads), 0, s, a.pair_z,
+                       a.ranges, a.work, tr, list, tk, tv);
+    return (int)hipGetLastError();
+}
+
 int launch_binning(BinArgs& a, hipStream_t s) {
+    if (per_tile_sort(a.vt, a.n_pairs, a.capacity)) return launch_binning_per_tile(a, s);
     const long long Q = a.n_pairs;
     // 1-2. stable depth sort of the visible pairs: the first pass reads every pair's depth
     //    key (pair_z; kNoDepth for a pair no view keeps) with the pair id as value, drops the
@@ -258,8 +646,9 @@ int launch_binning(BinArgs& a, hipStream_t s) {
     const unsigned egrid = (unsigned)((a.capacity + kEmitSlots - 1) / kEmitSlots > 0
                                           ? (a.capacity + kEmitSlots - 1) / kEmitSlots
                                           : 1);
-    hipLaunchKernelGGL(emit_kernel, dim3(egrid), dim3(kEmitThreads), 0, s, a.vt, a.records, dvals, a.emit_off,
-                       a.block_first, a.counters, a.capacity, a.tile_keys[first], a.tile_vals[first], a.ranges);
+    hipLaunchKernelGGL(emit_kernel<false>, dim3(egrid), dim3(kEmitThreads), 0, s, a.vt, a.records, dvals, a.emit_off,
+                       a.block_first, a.counters, a.capacity, a.tile_keys[first], a.tile_vals[first], nullptr,
+                       nullptr, a.ranges);
     // 5. stable sort by tile id
     uint32_t* tk[2] = {a.tile_keys[first], a.tile_keys[1 - first]};
     uint32_t* tv[2] = {a.tile_vals[first], a.tile_vals[1 - first]};
