@@ -49,7 +49,9 @@ class _RenderFn(torch.autograd.Function):
         st.capacity = buf.capacity
         ctx.st = st
         ctx.p = p
-        ctx.out = out
+        # aliases: keeping the returned tensors themselves would tie them and their graph into a cycle
+        # that holds the buffers until the garbage collector runs
+        ctx.out = tuple(t.detach() for t in out)
         ctx.buf = buf
         return out
 

@@ -396,8 +396,19 @@ class Rasterizer:
     def render(self, params: SplatParams, cams, views: ViewSpec, capacity: int | None = None,
                buf: Buffers | None = None, depth_var: bool = False):
         """Forward with automatic capacity growth (synchronises to read the counters).
-        Returns (out, buffers)."""
-        cap = capacity or (buf.capacity if buf is not None else max(1 << 16, 8 * views.n_pixels // 16))
+        Returns (out, buffers).
+
+        Without a known capacity the first guess is two intersections per (view, Gaussian) pair,
+        at least one per two pixels: scenes have 0.7 to 2.7 a pair, counting the culled ones, and
+        an overflow costs a whole second forward (a 150k-Gaussian render of three views and its
+        backward: 756 us with a guess by the pixels alone, 2 % too small, 423 by the pairs)."""
+        if capacity:
+            cap = capacity
+        elif buf is not None:
+            cap = buf.capacity
+        else:
+            n_pairs = sum(e - b for b, e in zip(views.g_begin, views.g_end))
+            cap = max(1 << 16, views.n_pixels // 2, 2 * n_pairs)
         while True:
             if buf is None or buf.capacity < cap:
                 buf = self.buffers(views, params.n, params.sh_degree, cap)
