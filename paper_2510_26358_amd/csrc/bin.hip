@@ -430,14 +430,23 @@ __global__ __launch_bounds__(256) void place_kernel(const uint32_t* tile_keys, c
         if (t[j] < n_tiles) out[base[t[j]] + r[j]] = q[j];
 }
 
-// One workgroup sorts a tile's list by (depth bits, pair id), a strict order: runs of 64 by each
-// element's rank among its run, then merges in which an element's place is its index in its own run plus
-// its rank in the other (a binary search), all in LDS up to kTileSortLds entries.  A longer list is
-// sorted in pieces of that length, which are then merged through global memory, between the pairs of
-// arrays (za, qa) and (zb, qb), ending in (zb, qb).  On entry the list is in qa; on exit its ids are in qb
-// and the tile's id in zb.  The workgroups follow the raster work order, the longest lists first.
+// One workgroup sorts a tile's list by (depth bits, pair id), a strict order.
+//
+// Up to kTileSortMost entries: by buckets of the depth bits between the list's least and greatest, then each
+// entry by its rank in its bucket, which holds a few; a chain of some ten dependent LDS accesses, where
+// merging takes a hundred for 1000 entries.  Where some bucket holds more than kBucketMost (equal depths, a far
+// outlier), and for the pieces of kTileSortLds entries of a longer list: runs of 64 by each element's
+// rank among its run, then merges in which an element's place is its index in its own run plus its rank in
+// the other (a binary search).  The pieces of a longer list are merged through global memory, between the
+// pairs of arrays (za, qa) and (zb, qb), ending in (zb, qb).  On entry the list is in qa; on exit its ids are
+// in qb and the tile's id in zb.  The workgroups follow the raster work order, the longest lists first.
+// One 960 x 600 view over 300k Gaussians (2280 lists, up to 1286 entries): 30 us by merges alone, 15
+// by buckets; three views over 600k 50 and 34.
 constexpr int kTileSortThreads = 256;
-constexpr int kTileSortLds = 1024;  // two buffers of 8 KB: eight workgroups on a CU
+constexpr int kTileSortLds = 1024;  // two buffers of 8 KB
+constexpr int kTileSortMost = 2 * kTileSortLds;
+constexpr int kTileSortItems = kTileSortMost / kTileSortThreads;
+constexpr int kBuckets = 1024, kBucketMost = 48;
 constexpr int kMergeItems = 4;  // searches a thread runs side by side
 
 // Orders the wave's own LDS accesses (which complete in order) for the compiler.
@@ -476,6 +485,105 @@ __device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, P
     }
 }
 
+// Sorts len <= kTileSortMost entries (ids q[0 .. len)) into a; false, and a undefined, if a bucket is too full.
+__device__ __forceinline__ bool bucket_sort(const uint32_t* q, const uint32_t* pair_z, int len, unsigned long long* a,
+                                            uint32_t (&first)[kBuckets + 1], uint32_t (&part)[3][4]) {
+    using u64 = unsigned long long;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    constexpr int BT = kBuckets / kTileSortThreads;
+    uint32_t id[kTileSortItems], z[kTileSortItems], lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int k = 0; k < kTileSortItems; ++k) {
+        const int i = t + k * kTileSortThreads;
+        if (i < len) id[k] = q[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kTileSortItems; ++k) {
+        const int i = t + k * kTileSortThreads;
+        if (i >= len) continue;
+        z[k] = pair_z[id[k]];
+        lo = min(lo, z[k]);
+        hi = max(hi, z[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < BT; ++k) first[BT * t + k] = 0u;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    }
+    if (lane == 0) {
+        part[0][w] = lo;
+        part[1][w] = hi;
+    }
+    __syncthreads();
+    lo = min(min(part[0][0], part[0][1]), min(part[0][2], part[0][3]));
+    hi = max(max(part[1][0], part[1][1]), max(part[1][2], part[1][3]));
+    const int bits = hi > lo ? 32 - __builtin_clz(hi - lo) : 0, shift = bits > 10 ? bits - 10 : 0;
+    uint32_t at[kTileSortItems];
+#pragma unroll
+    for (int k = 0; k < kTileSortItems; ++k)
+        if (t + k * kTileSortThreads < len) at[k] = atomicAdd(&first[(z[k] - lo) >> shift], 1u);
+    __syncthreads();
+    // counts to first places; the fullest bucket
+    uint32_t c[BT], sum = 0, most = 0;
+#pragma unroll
+    for (int k = 0; k < BT; ++k) {
+        c[k] = first[BT * t + k];
+        sum += c[k];
+        most = max(most, c[k]);
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
+        if (lane >= o) incl += y;
+        most = max(most, (uint32_t)__shfl_xor((int)most, o, 64));
+    }
+    if (lane == 63) {
+        part[2][w] = incl;
+        part[0][w] = most;
+    }
+    __syncthreads();
+    most = max(max(part[0][0], part[0][1]), max(part[0][2], part[0][3]));
+    if (most > (uint32_t)kBucketMost) {  // uniform over the workgroup
+        __syncthreads();                 // before `part` is written again
+        return false;
+    }
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int x = 0; x < 3; ++x) run += x < w ? part[2][x] : 0u;
+#pragma unroll
+    for (int k = 0; k < BT; ++k) {
+        first[BT * t + k] = run;
+        run += c[k];
+    }
+    if (t == kTileSortThreads - 1) first[kBuckets] = run;
+    __syncthreads();
+    uint32_t from[kTileSortItems], to[kTileSortItems];
+#pragma unroll
+    for (int k = 0; k < kTileSortItems; ++k) {
+        from[k] = to[k] = 0u;
+        if (t + k * kTileSortThreads >= len) continue;
+        const uint32_t b = (z[k] - lo) >> shift;
+        from[k] = first[b];
+        to[k] = first[b + 1];
+        a[from[k] + at[k]] = ((u64)z[k] << 32) | id[k];
+        at[k] = 0u;
+    }
+    __syncthreads();
+    for (uint32_t j = 0; j < most; ++j)
+#pragma unroll
+        for (int k = 0; k < kTileSortItems; ++k)
+            if (from[k] + j < to[k]) at[k] += a[from[k] + j] < (((u64)z[k] << 32) | id[k]) ? 1u : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTileSortItems; ++k)
+        if (t + k * kTileSortThreads < len) a[from[k] + at[k]] = ((u64)z[k] << 32) | id[k];
+    __syncthreads();
+    return true;
+}
+
 __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint32_t* pair_z, const uint32_t* ranges,
                                                                      const uint32_t* work, uint32_t* za,
                                                                      uint32_t* qa, uint32_t* zb, uint32_t* qb) {
@@ -486,6 +594,15 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
     if (tile == kNoTile) return;
     const uint2 se = reinterpret_cast<const uint2*>(ranges)[tile];
     const uint32_t n = se.y - se.x, s = se.x;
+    if (n == 0u) return;
+    __shared__ uint32_t first[kBuckets + 1], part[3][4];
+    if (n <= (uint32_t)kTileSortMost && bucket_sort(qa + s, pair_z, (int)n, buf[0], first, part)) {
+        for (uint32_t i = t; i < n; i += kTileSortThreads) {
+            zb[s + i] = tile;
+            qb[s + i] = (uint32_t)buf[0][i];
+        }
+        return;
+    }
     int levels = 0;  // merges through global memory
     while (((uint32_t)kTileSortLds << levels) < n) ++levels;
     for (uint32_t c0 = 0; c0 < n; c0 += kTileSortLds) {
@@ -582,8 +699,8 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
 // Which way a launch takes: the lists sorted tile by tile, or two radix sorts over all.  Tile by tile
 // is six launches (about 4.5 us each however little they do) against 23, but its atomics, scattered
 // places and merges cost more per intersection.  Binning of one 300k-Gaussian view (0.5M
-// intersections) 190 us by radix sorts, 67 tile by tile; three views over 600k (2.4M) 208 and 174; four
-// over 1M (7.5M) 304 and 378.  And one workgroup sorts a list, which beyond a few thousand entries takes
+// intersections) 190 us by radix sorts, 51 tile by tile; three views over 600k (2.4M) 208 and 158; four
+// over 1M (7.5M) 304 and 361.  And one workgroup sorts a list, which beyond a few thousand entries takes
 // longer than all the radix passes (a piece of 1024 about 7 us, a merge level of 4096 about 30): no list can
 // be longer than its view's Gaussian range, or the capacity leaves at most 512 entries a tile on average.
 constexpr long long kTileSortCapacity = 1ll << 22, kTileSortLongest = 4096, kTileSortMean = 512;
