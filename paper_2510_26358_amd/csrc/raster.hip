@@ -95,8 +95,8 @@ __device__ __forceinline__ bool needs_tests(float A, float B, float C, float o, 
 }
 
 // The base-2 exponent A' dx^2 + B' dx dy + C' dy^2 in one fixed order of roundings for both block shapes.
-// (The backward's two pixels a lane share A' dx instead, which rounds B' dx dy's product the other way
-// round: their alpha may differ from the forward's in its last bit.)
+// (SHARED, the backward of several pixels a thread: they share A' dx instead, which rounds the other of
+// the two products; alpha may differ from the forward's in its last bit.)
 __device__ __forceinline__ float exponent2(float A, float B, float C, float dx, float dy) {
     return __builtin_fmaf(dy, dy * C, dx * __builtin_fmaf(dx, A, dy * B));
 }
@@ -425,6 +425,147 @@ __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a)
             write_pixel(a, tc, px, py + 8 * k, C0[k], C1[k], C2[k], D[k], Tr[k], last[k], S2 ? &var[k] : nullptr);
 }
 
+// Several pixels a thread, and many tiles: the workgroup stages its tile's list in LDS, M entries at a
+// time, thread t covers column t % T and PPT rows.  Where px_per_thread asks for it and the chip is full
+// it is as fast as the wide blocks (22 views 507 and 500 us), and it keeps that shape's images: the compiler
+// forms the exponents of a thread's pixels in different orders of roundings, so the one order of the
+// block kernels moves alpha by an ulp, which is across the cutoff for a few pixels in 10^7.
+struct alignas(16) StagedRec {
+    float4 m, g0;  // z r g b | u v A' B'
+    float2 g1;     // C' o
+};
+
+template <int T, int PPT, int M, bool S2>
+__global__ __launch_bounds__(T* T / PPT) void raster_fwd_staged_kernel(RasterArgs a) {
+    constexpr int NT = T * T / PPT;
+    __shared__ StagedRec srec[M];
+    const uint32_t wt = a.work[blockIdx.x];
+    if (wt == kNoTile) return;  // padding of a shorter XCD list (whole workgroup)
+    const int tile = (int)wt;
+    const TileCoord tc = tile_coord(a.vt, tile);
+    const uint32_t start = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile]);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(a.ranges[2 * tile + 1]);
+    const int tid = threadIdx.x;
+
+    // A pixel that has stopped (or lies outside the image) gets cx = +inf: its exponent is
+    // then -inf (or NaN), below every threshold, so it keeps no further Gaussian without a
+    // separate flag test.
+    constexpr float kStopped = __builtin_huge_valf();
+    float cx[PPT], cy[PPT], Tr[PPT], C0[PPT], C1[PPT], C2[PPT], D[PPT], A[PPT], Mn[PPT], Sc[PPT];
+    uint32_t last[PPT];
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        const int lx = tid % T, ly = (tid / T) * PPT + k;
+        const int px = tc.px0 + lx, py = tc.py0 + ly;
+        cx[k] = (px < tc.W && py < tc.H) ? (float)px + 0.5f : kStopped;
+        cy[k] = (float)py + 0.5f;
+        Tr[k] = 1.f;
+        C0[k] = C1[k] = C2[k] = D[k] = A[k] = Mn[k] = Sc[k] = 0.f;
+        last[k] = 0;
+    }
+    const float amin = a.st.alpha_min, tmin = a.st.t_min;
+    const float amax = __builtin_canonicalizef(a.st.alpha_max);
+
+    for (uint32_t bs = start; bs < end; bs += M) {
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) any |= cx[k] != kStopped;
+        if (__syncthreads_count(any) == 0) break;
+#pragma unroll
+        for (int l = tid; l < M; l += NT) {
+            const uint32_t e = bs + l;
+            if (e < end) {
+                const Rec r = load_rec(a.records, a.tile_pairs[e]);
+                srec[l].m = make_float4(r.b.z, r.c.y, r.c.z, r.c.w);
+                srec[l].g0 = make_float4(r.a.x, r.a.y, -0.5f * kLog2e * r.a.z, -kLog2e * r.a.w);
+                srec[l].g1 = make_float2(-0.5f * kLog2e * r.b.x, r.b.y);
+            }
+        }
+        __syncthreads();
+        const uint32_t bend = end - bs > (uint32_t)M ? bs + M : end;
+        const char* sbase = reinterpret_cast<const char*>(srec);
+        uint32_t off = 0;  // byte offset of record e - bs in LDS
+        in_vgpr(off);
+        // entries in groups of eight: the later records are read at immediate offsets from the
+        // first's LDS address, so the address advances once per group, and the wave's early
+        // exit is tested once per group (entries past a wave's stop keep nothing: a stopped
+        // pixel's exponent is -inf or NaN)
+        auto entry = [&](const StagedRec& r, uint32_t e) {
+            const float4 r0 = r.g0;
+            const float2 r1 = r.g1;  // (C', o)
+            // all of the record's reads are issued here, before the tests that use them
+            asm volatile("" ::"v"(r0.x), "v"(r0.y), "v"(r0.z), "v"(r0.w), "v"(r1.x), "v"(r1.y));
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) {
+                // one predicate, one branch: the exp is cheap next to divergent control
+                const float dx = r0.x - cx[k], dy = r0.y - cy[k];
+                const float p2 = dx * (r0.z * dx + r0.w * dy) + r1.x * dy * dy;
+                const float alpha = fminf(amax, r1.y * __builtin_amdgcn_exp2f(p2));
+                const bool keep = p2 <= 0.f && alpha >= amin;
+                if (keep) {
+                    // stop (once per pixel) before a Gaussian that would take T below t_min;
+                    // the tested T (1 - alpha), one rounding, is the next T
+                    const float Tn = __builtin_fmaf(-alpha, Tr[k], Tr[k]);
+                    const bool go = Tn >= tmin;
+                    cx[k] = go ? cx[k] : kStopped;  // +inf marks the pixel stopped
+                    in_vgpr(cx[k]);                 // one select here, not moves in both branches
+                    if (go) {
+                        const float4 rc = r.m;  // (z, r, g, b)
+                        const float w = alpha * Tr[k];
+                        C0[k] += w * rc.y;
+                        C1[k] += w * rc.z;
+                        C2[k] += w * rc.w;
+                        D[k] += w * rc.x;
+                        if (S2) {
+                            A[k] += w;
+                            const float dz = rc.x - Mn[k];
+                            Mn[k] += dz * (w * __builtin_amdgcn_rcpf(A[k]));
+                            Sc[k] += w * dz * (rc.x - Mn[k]);
+                        }
+                        Tr[k] = Tn;
+                        last[k] = e - start + 1;
+                    }
+                }
+            }
+        };
+        auto wave_live = [&]() {
+            bool live = false;
+#pragma unroll
+            for (int k = 0; k < PPT; ++k) live |= cx[k] != kStopped;
+            return __ballot(live) != 0ull;  // wave-uniform: false once every pixel has stopped
+        };
+        for (uint32_t e = bs; e < bend; e += 8, off += 8 * sizeof(StagedRec)) {
+            if (!wave_live()) break;
+            entry(*reinterpret_cast<const StagedRec*>(sbase + off), e);
+#pragma unroll
+            for (int g = 1; g < 8; ++g) {
+                if (e + g == bend) break;
+                entry(*reinterpret_cast<const StagedRec*>(sbase + off + g * sizeof(StagedRec)), e + g);
+            }
+        }
+        __syncthreads();
+    }
+    const long long plane = (long long)tc.W * tc.H;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) {
+        const int lx = tid % T, ly = (tid / T) * PPT + k;
+        if (tc.px0 + lx >= tc.W || tc.py0 + ly >= tc.H) continue;
+        const long long p = (long long)(tc.py0 + ly) * tc.W + (tc.px0 + lx);
+        const long long gp = tc.pix0 + p;
+        float* rgb = a.rgb + 3 * tc.pix0;
+        rgb[p] = C0[k] + Tr[k] * a.st.bg0;
+        rgb[plane + p] = C1[k] + Tr[k] * a.st.bg1;
+        rgb[2 * plane + p] = C2[k] + Tr[k] * a.st.bg2;
+        a.depth[gp] = D[k];
+        if (S2) a.depth_var[gp] = Sc[k] + A[k] * Tr[k] * Mn[k] * Mn[k];
+        a.alpha[gp] = 1.f - Tr[k];
+        a.t_final[gp] = Tr[k];
+        a.last[gp] = last[k];
+        if (a.zero_px[0]) a.zero_px[0][gp] = 0.f;
+        if (a.zero_px[1]) a.zero_px[1][gp] = 0.f;
+    }
+}
+
 // ------------------------------------------------------------------------- backward
 //
 // PPT pixels a lane (8 x 8 PPT blocks), GRP entries a step: the exponents of a step are formed side by
@@ -435,7 +576,7 @@ __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a)
 // two small views 32 -> 24 us (41).  GA: the upstream adjoint has an alpha term (dL/dA); the fused
 // loss never has one.  S2: the loss has an adjoint for the second depth moment sum w z^2 (rendered
 // variance).
-template <int T, int PPT, int GRP, bool GA, bool S2>
+template <int T, int PPT, int GRP, bool GA, bool S2, bool SHARED>
 __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a) {
     constexpr int NW = T * T / PPT / 64, COLS = T / 8;
     __shared__ Rows<GRP> rows[NW];
@@ -564,8 +705,8 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                     for (int k = 0; k < PPT; ++k) {
                         const float dy = r0[i].y - cy[k];
                         const float p2 =
-                            PPT == 1 ? exponent2(r0[i].z, r0[i].w, r1[i].x, dx, dy)
-                                     : __builtin_fmaf(dy, dy * r1[i].x, dx * __builtin_fmaf(r0[i].w, dy, Adx));
+                            !SHARED ? exponent2(r0[i].z, r0[i].w, r1[i].x, dx, dy)
+                                    : __builtin_fmaf(dy, dy * r1[i].x, dx * __builtin_fmaf(r0[i].w, dy, Adx));
                         araw[i][k] = r1[i].y * __builtin_amdgcn_exp2f(p2);
                         km[i][k] = __builtin_amdgcn_uicmp(j[i], last[k], 36) &  // j < last
                                    le_mask(amin, TESTS ? fminf(amax, araw[i][k]) : araw[i][k]);
@@ -707,8 +848,8 @@ static bool wide_blocks(const ViewTable& vt, int T) {
     return T > 8 && (long long)vt.tile_base[vt.n_views] * (T * T / 128) >= 8192;
 }
 
-// `batch` and `ppt` only name a supported shape: how many entries and pixels a lane takes follows
-// from the number of blocks.
+// How many entries and pixels a lane takes follows from the number of blocks; `batch` and `ppt` name a
+// supported shape, and ppt > 1 the staged forward for many tiles and the backward's shared exponents.
 static bool shape_supported(int T, int batch, int ppt) {
 #define X(t_, p_, m_) \
     if (T == t_ && ppt == p_ && batch == m_) return true;
@@ -723,32 +864,42 @@ int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_
     if (!shape_supported(T, batch, ppt)) return AGS_ERR_NOT_SUPPORTED;
     auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3(nb), dim3(threads), 0, s, a); };
     const bool wide = wide_blocks(a.vt, T), var = a.depth_var != nullptr;
+    if (wide && ppt > 1) {
+#define X(t_, p_, m_)                                                                                          \
+    if constexpr (p_ > 1)                                                                                      \
+        if (T == t_ && ppt == p_ && batch == m_)                                                               \
+            var ? launch(raster_fwd_staged_kernel<t_, p_, m_, true>, t_ * t_ / p_)                             \
+                : launch(raster_fwd_staged_kernel<t_, p_, m_, false>, t_ * t_ / p_);
+        AGS_RASTER_CONFIGS(X)
+#undef X
+        return 0;
+    }
     if (T == 8) var ? launch(raster_fwd_kernel<8, true>, 64) : launch(raster_fwd_kernel<8, false>, 64);
-    else if (T == 16 && wide) var ? launch(raster_fwd_wide_kernel<16, true>, 128) : launch(raster_fwd_wide_kernel<16, false>, 128);
+    else if (wide) var ? launch(raster_fwd_wide_kernel<16, true>, 128) : launch(raster_fwd_wide_kernel<16, false>, 128);
     else if (T == 16) var ? launch(raster_fwd_kernel<16, true>, 256) : launch(raster_fwd_kernel<16, false>, 256);
-    else if (wide) var ? launch(raster_fwd_wide_kernel<32, true>, 512) : launch(raster_fwd_wide_kernel<32, false>, 512);
     else var ? launch(raster_fwd_kernel<32, true>, 1024) : launch(raster_fwd_kernel<32, false>, 1024);
     return 0;
 }
 
-template <int T, int PPT, int GRP>
+template <int T, int PPT, int GRP, bool SHARED>
 static void bwd_variant(const RasterBwdArgs& a, int nb, hipStream_t s) {
-    const dim3 grid(nb), block(T * T / PPT);
-    if (!a.loss_mode && a.d_alpha) hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, true, false>), grid, block, 0, s, a);
-    else if (a.loss_mode && a.d_depth2) hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, false, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((raster_bwd_kernel<T, PPT, GRP, false, false>), grid, block, 0, s, a);
+    const bool ga = !a.loss_mode && a.d_alpha, s2 = a.loss_mode && a.d_depth2;
+    const auto kernel = ga   ? raster_bwd_kernel<T, PPT, GRP, true, false, SHARED>
+                        : s2 ? raster_bwd_kernel<T, PPT, GRP, false, true, SHARED>
+                             : raster_bwd_kernel<T, PPT, GRP, false, false, SHARED>;
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(T * T / PPT), 0, s, a);
 }
 
 int launch_raster_bwd(const RasterBwdArgs& a, int T, int batch, int ppt, hipStream_t s) {
     const int nb = raster_blocks(a.vt);
     if (nb <= 0) return 0;
     if (!shape_supported(T, batch, ppt)) return AGS_ERR_NOT_SUPPORTED;
-    const bool wide = wide_blocks(a.vt, T);
-    if (T == 8) bwd_variant<8, 1, 4>(a, nb, s);
-    else if (T == 16 && wide) bwd_variant<16, 2, 2>(a, nb, s);
-    else if (T == 16) bwd_variant<16, 1, 4>(a, nb, s);
-    else if (wide) bwd_variant<32, 2, 2>(a, nb, s);
-    else bwd_variant<32, 1, 4>(a, nb, s);
+    const bool wide = wide_blocks(a.vt, T), shared = ppt > 1;
+    if (T == 8) bwd_variant<8, 1, 4, false>(a, nb, s);
+    else if (T == 16 && wide) shared ? bwd_variant<16, 2, 2, true>(a, nb, s) : bwd_variant<16, 2, 2, false>(a, nb, s);
+    else if (T == 16) shared ? bwd_variant<16, 1, 4, true>(a, nb, s) : bwd_variant<16, 1, 4, false>(a, nb, s);
+    else if (wide) bwd_variant<32, 2, 2, true>(a, nb, s);  // tiles of 32 have two or four pixels a thread
+    else bwd_variant<32, 1, 4, true>(a, nb, s);
     return 0;
 }
 

@@ -5,11 +5,12 @@ A launch of few tiles gives each wave an 8 x 8 block, one of at least 8192 8 x 1
 small ragged view is rendered alone (8 x 8 blocks) and beside a large view that sees nothing (8 x 16
 blocks), with lists that end just below, at and above one chunk and with records that need the
 per-pixel tests (opacity above the alpha clamp; a conic near singular).  The two images are the same
-bit for bit: every decision and every sum over a pixel's list is made in the same order.  Loss and
-gradients, summed over pixels in another order, are each held to the oracle at the path's tolerance;
-not with the near-singular conics, whose exponent cancels in single precision (an ellipse of 240 by
-0.5 pixels at 45 degrees has terms of 6000, so an error of 4e-4 in its exponent and more in its
-gradients, whichever way they are summed).
+bit for bit: every decision and every sum over a pixel's list is made in the same order.  (With several
+pixels a thread the large launch takes the staged kernel, which rounds the exponent differently.)
+Images, loss and gradients of every shape are each held to the oracle at the path's tolerance; not
+with the near-singular conics, whose exponent cancels in single precision (an ellipse of 240 by 0.5
+pixels at 45 degrees has terms of 6000, so an error of 4e-4 in its exponent and more in its gradients,
+whichever way they are summed).
 """
 import numpy as np
 import pytest
@@ -24,7 +25,7 @@ from tests.oracle_helpers import camera, random_scene
 pytestmark = pytest.mark.gpu
 
 NAMES = ["means", "log_scales", "quats", "opacity_logits", "sh"]
-SHAPE = {8: (64, 1), 16: (256, 1), 32: (256, 4)}
+SHAPES = [(8, 64, 1), (16, 256, 1), (16, 128, 2), (16, 64, 4), (32, 512, 2), (32, 256, 4)]
 LARGE = 1024  # 4096 tiles of 16 x 16, 1024 of 32 x 32: with it a launch is just over the line
 CASES = [(1, 7, 5), (64, 67, 45), (65, 33, 50), (200, 67, 45)]
 
@@ -45,17 +46,17 @@ def _scene(n, width, height, thin, large):
     return sc
 
 
-def _rasterizer(tile):
+def _rasterizer(shape):
     from paper_2510_26358_amd.rasterizer import Rasterizer
-    return Rasterizer(0, tile=tile, batch=SHAPE[tile][0], px_per_thread=SHAPE[tile][1])
+    return Rasterizer(0, tile=shape[0], batch=shape[1], px_per_thread=shape[2])
 
 
 @pytest.mark.parametrize("thin", [False, True])
-@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[2] == 1], ids=str)
 @pytest.mark.parametrize("n,width,height", CASES)
-def test_images_do_not_depend_on_the_block_shape(tile, n, width, height, thin):
-    ras = _rasterizer(tile)
-    print("tile", tile, "n", n, "thin", thin, flush=True)
+def test_images_do_not_depend_on_the_block_shape(shape, n, width, height, thin):
+    ras = _rasterizer(shape)
+    print("shape", shape, "n", n, "thin", thin, flush=True)
     a = run_forward(_scene(n, width, height, thin, False), ras, depth_var=thin)[0][0]
     b, c = run_forward(_scene(n, width, height, thin, True), ras, depth_var=thin)[0]
     assert a["alpha"].max() > 0.1
@@ -74,12 +75,12 @@ def _reference(*key):
 
 
 @pytest.mark.parametrize("large", [False, True])
-@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
 @pytest.mark.parametrize("n,width,height", CASES)
-def test_both_block_shapes_match_the_oracle(tile, n, width, height, large):
+def test_both_block_shapes_match_the_oracle(shape, n, width, height, large):
     fwd, ref = _reference(n, width, height)
-    print("tile", tile, "n", n, "large", large, flush=True)
-    g = run_loss_backward(_scene(n, width, height, False, large), _rasterizer(tile), w_l1=0.8, lam=0.5)
+    print("shape", shape, "n", n, "large", large, flush=True)
+    g = run_loss_backward(_scene(n, width, height, False, large), _rasterizer(shape), w_l1=0.8, lam=0.5)
     v, r = g["fwd"][0], fwd[0]
     ok = ~r["ambiguous"]
     assert np.abs(v["rgb"].reshape(3, -1)[:, r["pix"]].T - r["rgb"])[ok].max(initial=0) <= TOL_RGB
