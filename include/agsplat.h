@@ -67,8 +67,9 @@ enum {
  * one pixel per thread, backward shape = forward shape.  The supported (tile, batch,
  * pixels per thread) launch shapes are (8,64,1) (8,128,1) (16,128,1) (16,256,1) (16,64,2)
  * (16,128,2) (16,256,2) (16,64,4) (32,256,4) (32,512,2); others give AGS_ERR_NOT_SUPPORTED at
- * launch.  Of a shape the tile size selects a kernel; how many list entries and pixels a lane
- * takes follows from the number of tiles in the launch. */
+ * launch.  The kernels take list entries and pixels per lane by the number of tiles in the launch;
+ * several pixels per thread select the forward that stages whole tiles when there are many of them,
+ * and share part of the exponent in the backward. */
 typedef struct ags_config {
     float alpha_min, alpha_max, t_min, blur, z_near, fov_clamp;
     float bg[3];

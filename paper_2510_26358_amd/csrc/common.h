@@ -515,8 +515,8 @@ struct RasterArgs {
     // zeroed per pixel (or null): the backward's dense depth and second-moment adjoints
     float* zero_px[2];
 };
-// The (tile, pixels per thread, LDS batch) shapes that a configuration may name (the raster kernels
-// take their blocks by the number of tiles, not by the last two): writes up to n_max of them and
+// The (tile, pixels per thread, LDS batch) shapes that a configuration may name (of the last two
+// the raster kernels take only whether a thread has several pixels): writes up to n_max of them and
 // returns how many there are.
 int raster_shapes(int* tile, int* ppt, int* batch, int n_max);
 int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_t s);

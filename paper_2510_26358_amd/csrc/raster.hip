@@ -316,7 +316,7 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
 
 // 8 x 16 blocks, two pixels a lane eight rows apart (the same dx), two entries a step, plain fmas: one
 // read of a record serves two pixels, which keeps the LDS behind the vector units.  4-view 1280 x 800
-// step over 1M Gaussians 195 -> 173 us, over 2M 246 -> 204 us, 22 views over 2.9M 507 -> 480 us.
+// step over 1M Gaussians 195 -> 173 us, over 2M 246 -> 204 us.
 // No prefetch: it costs two of eight waves a SIMD (rig step 177 -> 192 us).
 template <int T, bool S2>
 __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a) {
