@@ -62,7 +62,7 @@ struct Layout {
     size_t f_pair_z, f_dkeys0, f_dkeys1, f_dvals0, f_dvals1, f_emit_off, f_block_first, f_tkeys0, f_tkeys1,
         f_tvals1, f_hist, f_rowtot, f_block_sums, f_tile_count, f_total;
     // bwd ws
-    size_t b_dssim, b_partials, b_pose_part, b_vis, b_total;
+    size_t b_dssim, b_partials, b_pose_part, b_total;
     long long n_partials, n_ssim;
 };
 
@@ -175,7 +175,6 @@ int build_layout(const ags_config* cfg, const ags_views* views, int n, long long
     L.b_partials = o; o = align_up(o + (size_t)L.n_partials * 4);
     L.b_pose_part = o; o = align_up(o + (size_t)2 * (project_bwd_blocks(n) > 0 ? project_bwd_blocks(n) : 1) *
                                          views->n_views * 6 * 4);
-    L.b_vis = o; o = align_up(o + (size_t)(n > 0 ? n : 1) * 4);
     L.b_total = o;
     return AGS_OK;
 }
@@ -688,7 +687,6 @@ int render_bwd(ags_ctx* ctx, const ags_views* views, const ags_gaussians* g, con
         pa.g_pose = grads->pose;
         pa.accumulate = grads->accumulate;
         pa.pose_partials = at<float>(ws, L.b_pose_part);
-        pa.vis_mask = at<uint32_t>(ws, L.b_vis);
         pa.stat_grad = grads->stat_grad;
         pa.stat_count = grads->stat_count;
         pa.fused_adam = fused != nullptr;

@@ -635,7 +635,6 @@ struct ProjectBwdArgs {
     const float* grad2d;
     float *g_means, *g_log_scales, *g_quats, *g_logits, *g_sh, *g_pose;
     float* pose_partials;  // [n_views * 6][2 project_bwd_blocks(n)]: geometry, then colour
-    uint32_t* vis_mask;    // [n]: views keeping each Gaussian (geometry phase -> colour phase)
     float* stat_grad;      // [n] or null: += |dL/d(u, v)| per view seeing the Gaussian
     float* stat_count;     // [n] or null: += number of those views
     int accumulate;
