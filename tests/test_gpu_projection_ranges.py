@@ -1,4 +1,4 @@
-"""Projection backward over views whose Gaussian ranges differ.
+"""Projection over views whose Gaussian ranges differ, and the rows it clears for the backward.
 
 A wave handles 64 Gaussians, skips the views whose range misses them and loads the pair counts of the
 others four at a time; the lanes outside a view's range must take nothing from it.  Ranges that are
@@ -46,3 +46,32 @@ def test_gradients_over_ragged_ranges_match_the_oracle(sh_degree, n_views):
         assert good, (name, msg)
     good, msg = grad_close(got["pose"], ref["pose"])
     assert good, ("pose", msg)
+
+
+@pytest.mark.parametrize("spread", [0.2, 3.0])  # every Gaussian in sight, or about one in seven
+@pytest.mark.parametrize("n", [1, 16, 17, 63, 64, 65, 130])
+def test_the_forward_clears_every_kept_pairs_sums(n, spread):
+    """A second step into the same buffers, whose adjoint rows hold the first step's sums: four lanes
+    clear a row and a store sixteen, whatever subset of a wave is kept."""
+    import torch
+    from paper_2510_26358_amd.rasterizer import LossTargets, Rasterizer
+    from tests.gpu_helpers import run_forward
+    sc = random_scene(800 + n, n=n, sh_degree=1, width=33, height=21)
+    sc.means[:] = np.random.default_rng(n).uniform(-spread, spread, (n, 3)) + [0.0, 0.0, 4.0]
+    sc.means[0] = [0.0, 0.0, 3.0]
+    ras = Rasterizer(0)
+    print("n", n, "spread", spread, flush=True)
+    _, (p, cams, views, out, buf) = run_forward(sc, ras)
+    targets = LossTargets.from_scene(sc, views, w_l1=0.8, lambda_lidar=0.5)
+    steps = []
+    for _ in range(2):
+        ras.forward_into(p, cams, views, buf, out)
+        grads, pose = p.zeros_like(), torch.zeros(1, 6, device="cuda")
+        ras.backward_into(p, cams, views, buf, out, grads, pose, loss=targets,
+                          loss_out=torch.zeros(1, device="cuda"))
+        torch.cuda.synchronize()
+        steps.append([t.cpu().numpy() for t in grads.tensors()] + [pose.cpu().numpy()])
+    assert np.abs(steps[0][0]).max() > 0
+    for a, b in zip(*steps):
+        good, msg = grad_close(b, a)
+        assert good, msg
