@@ -231,6 +231,15 @@ __device__ __forceinline__ T* sh_row(T* base, int n, int r) {
     return base + (size_t)r * (size_t)n;
 }
 
+// Workgroup -> block of work for compactions, whose blocks write runs that start anywhere in a line: strips
+// of `strip` consecutive blocks go to one XCD (workgroup g runs on XCD g % 8), so that the neighbour that
+// writes the rest of a line is on the same L2.  A launch row has run_grid(n_blocks, strip) workgroups.
+inline unsigned run_grid(unsigned n_blocks, unsigned strip) { return (n_blocks + 8 * strip - 1) / (8 * strip) * 8 * strip; }
+__device__ __forceinline__ unsigned run_block(unsigned g, unsigned strip) {
+    const unsigned k = g >> 3;
+    return (k / strip * 8 + (g & 7)) * strip + k % strip;
+}
+
 // Returns p unchanged but opaque to the optimiser (an empty asm on a scalar register), so
 // addresses derived from it inside a loop are not hoisted into long-lived vector registers.
 template <typename T>

@@ -254,6 +254,7 @@ struct RebuildArgs {
     int F, k3, chunks;
     long long n_keep;
     long long q_begin, q_end;       // the listed rows this launch moves
+    unsigned strip;                 // blocks of a strip (run_block)
     long long reload_off;           // reload rank of stage_in's first row
     long long evict_off;            // offload rank of stage_out's (and evict_ids') first row
     const float* in[3][5];
@@ -301,7 +302,7 @@ __device__ __forceinline__ void map_move(const float* __restrict__ src, long lon
 // means, log-scales, quaternion and logit (and the row's id bookkeeping); chunks 1.. = SH
 // rows in groups of kMapRows.
 __global__ __launch_bounds__(kMapThreads) void map_rebuild_kernel(RebuildArgs a, MapDev m) {
-    const long long q = a.q_begin + (long long)blockIdx.x * kMapThreads + threadIdx.x;
+    const long long q = a.q_begin + (long long)run_block(blockIdx.x, a.strip) * kMapThreads + threadIdx.x;
     if (q >= a.q_end) return;
     const int t = blockIdx.y / a.chunks, c = blockIdx.y % a.chunks;
     const bool evict = a.evict_flag && a.evict_flag[q];
@@ -878,7 +879,12 @@ int ags_map_insert(ags_map* mp, const float* points, const float* colors, int64_
         a.q_end = q1;
         a.reload_off = r_off;
         a.evict_off = e_off;
-        hipLaunchKernelGGL(map_rebuild_kernel, dim3(grid_of(q1 - q0), 3 * a.chunks), dim3(kMapThreads), 0, s, a, m);
+        // The kept rows' new stride starts them anywhere in a line (629k rows: 190 us with every eighth block
+        // on an XCD, 187 with strips of 4, 172 with 16).  Offloaded rows are a run of their own, written
+        // splat by splat, which long strips give to few XCDs (405k rows, a quarter offloaded: 326, 323 and 344).
+        a.strip = a.evict_flag ? 4u : 16u;
+        hipLaunchKernelGGL(map_rebuild_kernel, dim3(run_grid(grid_of(q1 - q0), a.strip), 3 * a.chunks),
+                           dim3(kMapThreads), 0, s, a, m);
     };
     // offloaded rows [0, e) of the staging into the host store, on the caller's thread
     auto store_offloads = [&](long long e) -> int {
