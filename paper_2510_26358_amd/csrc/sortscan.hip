@@ -256,11 +256,20 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__device__ __forceinline__ void chunk_of_block(long long n, int grid, long long& start, long long& end) {
+// This workgroup's chunk of the input.  The chunks that hold items are dealt to the XCDs in runs
+// (workgroup g runs on XCD g % 8; the empty ones keep their number): neighbouring chunks write
+// neighbouring pieces of each digit's output and neighbouring counts, so the lines that they share are put
+// together in one L2.  All passes of a launch: 4 views over 2M Gaussians 350 -> 332 us (counting 70 -> 59), over 1M
+// 216 -> 210, 22 views over 2.9M 432 -> 428.  Runs over the whole grid instead leave XCDs without items
+// where few are kept (22 views: 438).
+__device__ __forceinline__ int chunk_of_block(long long n, int grid, long long& start, long long& end) {
     const long long chunk = ((n + grid - 1) / grid + kSortTile - 1) / kSortTile * kSortTile;
-    start = (long long)blockIdx.x * chunk;
+    const int g = blockIdx.x, live = chunk > 0 ? (int)((n + chunk - 1) / chunk) : 0;
+    const int c = g < live ? (g & 7) * (live >> 3) + min(g & 7, live & 7) + (g >> 3) : g;
+    start = (long long)c * chunk;
     end = start + chunk < n ? start + chunk : n;
     if (start > n) start = n;
+    return c;
 }
 
 // Exclusive scan of one value per thread over a kSortThreads workgroup; total returned.
@@ -292,7 +301,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(
     __shared__ uint32_t h[256];
     const long long n = live_count(n_max, n_dev);
     long long start, end;
-    chunk_of_block(n, grid, start, end);
+    const int c = chunk_of_block(n, grid, start, end);
     h[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t mask = (1u << dbits) - 1u;
@@ -311,7 +320,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_count_kernel(
         }
     }
     __syncthreads();
-    hist[(long long)threadIdx.x * grid + blockIdx.x] = h[threadIdx.x];
+    hist[(long long)threadIdx.x * grid + c] = h[threadIdx.x];
 }
 
 // Workgroup d: exclusive scan of row d (grid <= kSortMaxGrid entries, 4 consecutive ones per
@@ -357,10 +366,10 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
     // the digit offsets, the live count and then the first tile's items are loaded before the
     // prologue's barriers, so their round trips overlap instead of following one another
     const uint32_t my_rowtot = rowtot[t];
-    const uint32_t my_hist = hist[(long long)t * grid + blockIdx.x];
     const long long n = live_count(n_max, n_dev);
     long long start, end;
-    chunk_of_block(n, grid, start, end);
+    const int c = chunk_of_block(n, grid, start, end);
+    const uint32_t my_hist = hist[(long long)t * grid + c];
     uint32_t kv[kSortItems], vv[kSortItems];
     auto load_tile = [&](long long base) {
         const int nt = end - base < kSortTile ? (int)(end - base) : kSortTile;
