@@ -110,7 +110,8 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectArgs a) {
         const unsigned long long kept = __ballot(cnt != 0u);
         const int n_kept = __popcll(kept);
         if (n_kept) {
-            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
             // lane r takes the number of the r-th kept lane (slot 63 is free unless all are kept)
             const int who = __builtin_amdgcn_ds_permute((cnt ? rank : 63) << 2, lane);
             float4* rows = reinterpret_cast<float4*>(a.grad2d + (q - lane) * kGrad2dStride);
