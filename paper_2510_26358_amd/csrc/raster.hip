@@ -110,6 +110,12 @@ __device__ __forceinline__ int rank_in(unsigned long long m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Whether a record's colour or depth is infinite, NaN or beyond 1e15 (in any channel, or their sum): 0 times it
+// may then not be 0, so it stays out of sums that also run over pixels which do not keep the record.
+__device__ __forceinline__ bool unbounded(float r, float g, float b, float z) {
+    return !(fabsf(r) + fabsf(g) + fabsf(b) + fabsf(z) <= 1e15f);
+}
+
 // Keeps a value in a vector register from here on.
 template <typename V>
 __device__ __forceinline__ void in_vgpr(V& v) {
@@ -209,7 +215,9 @@ __device__ __forceinline__ void write_pixel(const RasterArgs& a, const TileCoord
 // 4k: 22 -> 12 us).  The colour is a contraction over the entries, C[ch][pixel] += c[ch] w[pixel], which
 // v_mfma_f32_4x4x1_16b_f32 does with the pixel's four sums in its own lane: one LDS read a step gives
 // the colours of all four entries, where broadcast reads kept the LDS 80 % busy.  It rounds like the
-// four fmas it replaces.  S2: also output the rendered depth variance.
+// four fmas it replaces, but runs over all lanes, of which those that do not keep the entry have w = 0: a
+// chunk with an unbounded colour takes the fmas, on the lanes that keep it.  S2: also output the rendered
+// depth variance.
 template <int T, bool S2>
 __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
     constexpr int NW = T * T / 64, COLS = T / 8, GRP = 4;
@@ -257,13 +265,15 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
         const bool in = e < end && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, Y0, 7.f, 7.f);
         bool slow;
         const int n = my.pack(r, in, e - start + 1, amax, slow);
+        const bool far = __builtin_amdgcn_ballot_w64(in && unbounded(r.c.y, r.c.z, r.c.w, r.b.z)) != 0ull;
         int lastc = -1;  // the last contributor's row in this chunk
-        auto run = [&](auto tests) {
+        auto run = [&](auto tests, auto matrix) {
             int row = 0;
             in_vgpr(row);
             for (int g = 0; g < n && open != 0ull; g += GRP, row += GRP) {
                 // lanes 4 i .. 4 i + 3 hold the channels of the step's entry i (i < 4)
-                const float colv = reinterpret_cast<const float*>(my.col + g)[lane & 15];
+                float colv = 0.f;
+                if (decltype(matrix)::value) colv = reinterpret_cast<const float*>(my.col + g)[lane & 15];
                 float4 r0[GRP];
                 float2 r1[GRP];
 #pragma unroll
@@ -292,9 +302,19 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
                     const float Tn = __builtin_fmaf(-al[i], Tr, Tr);
                     const unsigned long long go = le_mask(tmin, Tn) & km;
                     open &= ~(km ^ go);
-                    const float w = lane_of(go) ? al[i] * Tr : 0.f;
-                    C = __builtin_amdgcn_mfma_f32_4x4x1f32(colv, w, C, 4, i, 0);
+                    if (decltype(matrix)::value) {
+                        const float w = lane_of(go) ? al[i] * Tr : 0.f;
+                        C = __builtin_amdgcn_mfma_f32_4x4x1f32(colv, w, C, 4, i, 0);
+                    }
                     if (lane_of(go)) {
+                        if (!decltype(matrix)::value) {
+                            const float4 c = my.col[g + i];
+                            const float w = al[i] * Tr;
+                            C[0] = __builtin_fmaf(w, c.x, C[0]);
+                            C[1] = __builtin_fmaf(w, c.y, C[1]);
+                            C[2] = __builtin_fmaf(w, c.z, C[2]);
+                            C[3] = __builtin_fmaf(w, c.w, C[3]);
+                        }
                         if (S2) var.add(al[i], Tr, my.col[g + i].w);
                         Tr = Tn;
                         lastc = row + i;
@@ -306,8 +326,9 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
                 blend(std::integral_constant<int, 3>{});
             }
         };
-        if (slow) run(std::true_type{});
-        else run(std::false_type{});
+        if (far) run(std::true_type{}, std::false_type{});
+        else if (slow) run(std::true_type{}, std::true_type{});
+        else run(std::false_type{}, std::true_type{});
         if (lastc >= 0) last = my.pos[lastc];
         __builtin_amdgcn_wave_barrier();
     }
