@@ -672,6 +672,12 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
             wlast = max(wlast, last[k]);
         }
     }
+    // an adjoint, or from the first record on that has one a colour, that makes dL/dalpha infinite or NaN: it must not
+    // reach the sums of p of the records that its pixel does not keep
+    bool far = false;
+#pragma unroll
+    for (int k = 0; k < PPT; ++k) far |= unbounded(gC0[k], gC1[k], gC2[k], gD[k]) || unbounded(gX[k], 0.f, 0.f, 0.f);
+    far = __builtin_amdgcn_ballot_w64(far) != 0ull;
     if (a.loss_mode) {
         // tile sum of the L1 partials (deterministic order)
         float s = wave_sum(loss_part);
@@ -704,6 +710,7 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
         if (in) mypair[rank_in(__builtin_amdgcn_ballot_w64(in))] = q;
         bool slow;
         const int n = my.pack(r, in, (uint32_t)e, amax, slow);
+        far |= __builtin_amdgcn_ballot_w64(in && unbounded(r.c.y, r.c.z, r.c.w, r.b.z)) != 0ull;
         auto run = [&](auto tests) {
             constexpr bool TESTS = decltype(tests)::value;
             for (int g = 0; g < n; g += GRP) {
@@ -757,7 +764,7 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                         U[k] += w * qv;
                         Tr[k] = Tk;
                         // dL/dpower = alpha dL/dalpha (none where the alpha_max clamp is active)
-                        h[k] = TESTS && !(araw[i][k] <= amax) ? 0.f : ga * ak;
+                        h[k] = TESTS && !(lane_of(km[i][k]) && araw[i][k] <= amax) ? 0.f : ga * ak;
                         // depth adjoint: d(w z)/dz = w, d(w z^2)/dz = 2 w z
                         const float gz = S2 ? gD[k] + 2.f * z * gX[k] : gD[k];
                         c[0] = k == 0 ? w * gC0[k] : c[0] + w * gC0[k];
@@ -779,7 +786,7 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
                 }
             }
         };
-        if (slow) run(std::true_type{});
+        if (slow || far) run(std::true_type{});
         else run(std::false_type{});
         __builtin_amdgcn_wave_barrier();
     }

@@ -7,6 +7,7 @@ same scene under a finite colour of that channel.
 """
 import numpy as np
 import pytest
+import torch
 
 from oracle.render import render
 from oracle.settings import RenderSettings
@@ -51,3 +52,33 @@ def test_an_infinite_colour_stays_with_its_pixels(opacity):
         assert same.all(), k
         assert np.array_equal(a[k], b[k]), k
         assert not empty[k].any()
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("ppt_bwd", [1, 2])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_an_unbounded_alpha_adjoint_stays_with_its_pixel(value, ppt_bwd, large):
+    """One pixel's dL/dalpha without bounds (a ratio by an alpha of zero): the Gaussians that the pixel keeps have
+    unbounded gradients, the others the ones that they have with zero there."""
+    from paper_2510_26358_amd.rasterizer import Rasterizer
+    ras = Rasterizer(0, batch_bwd=128, px_per_thread_bwd=ppt_bwd)
+    _, (p, cams, views, out, buf) = run_forward(_scene(1.0, large, 1.0), ras)
+    pix = 67 * 21 + 30
+    assert 0.05 < float(out[2][pix]) < 0.99
+
+    def grads_of(at_pixel, others):
+        up = torch.full((views.n_pixels,), others, device="cuda")
+        up[pix] = at_pixel
+        g, pose = p.zeros_like(), torch.zeros(views.n_views, 6, device="cuda")
+        ras.backward_into(p, cams, views, buf, out, g, pose, upstream=(None, None, up))
+        torch.cuda.synchronize()
+        return [x.reshape(p.n, -1) for x in g.to_numpy_aos()]
+
+    kept = np.any(grads_of(1.0, 0.0)[0] != 0, axis=1)
+    assert 0 < kept.sum() < p.n / 2
+    want, got = grads_of(0.0, 1.0), grads_of(value, 1.0)
+    for a, b in zip(got, want):
+        # float atomics: the order of at most a few hundred additions
+        assert np.abs(a[~kept] - b[~kept]).max() <= 1e-4 * np.abs(b).max()
+    assert not np.isfinite(got[0][kept]).any()
+    assert not got[4].any()  # an alpha adjoint has no colour part
