@@ -226,6 +226,7 @@ BinArgs bin_args(const Layout& L, void* saved, void* ws) {
     a.records = at<float>(saved, L.s_records);
     a.pair_count = at<uint32_t>(saved, L.s_pair_count);
     a.pair_z = at<uint32_t>(ws, L.f_pair_z);
+    a.given_depths = false;
     a.counters = at<uint32_t>(saved, L.s_counters);
     a.n_pairs = L.Q;
     a.capacity = L.cap;
@@ -509,7 +510,9 @@ int ags_bin_records(ags_ctx* ctx, const ags_views* views, int32_t n_gaussians, c
                              hipMemcpyDeviceToDevice, s);
     launch_count_from_records(L.vt, records, valid, L.Q, at<uint32_t>(saved, L.s_pair_count),
                               at<uint32_t>(ws, L.f_pair_z), s);
-    run_binning(bin_args(L, saved, ws), s);
+    BinArgs ba = bin_args(L, saved, ws);
+    ba.given_depths = true;
+    run_binning(ba, s);
     return hip_status(ctx);
 }
 

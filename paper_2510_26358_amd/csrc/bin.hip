@@ -277,8 +277,10 @@ __device__ __forceinline__ uint2 block_inclusive2(uint2 v, uint2* wave_tot, uint
     return v;
 }
 
-__device__ __forceinline__ void load_counts(const uint32_t* pair_count, long long n, long long i0,
-                                            uint32_t (&c)[kPairItems]) {
+// pair_z: null where a pair with a count has a depth (the projection's); given records may hold a NaN whose
+// bits are kNoDepth, and such a pair is listed nowhere, as in the depth sort.
+__device__ __forceinline__ void load_counts(const uint32_t* pair_count, const uint32_t* pair_z, long long n,
+                                            long long i0, uint32_t (&c)[kPairItems]) {
     if (i0 + kPairItems <= n) {  // i0 is a multiple of 8: 16-byte aligned
         const uint4 p = reinterpret_cast<const uint4*>(pair_count + i0)[0];
         const uint4 q = reinterpret_cast<const uint4*>(pair_count + i0)[1];
@@ -288,16 +290,22 @@ __device__ __forceinline__ void load_counts(const uint32_t* pair_count, long lon
 #pragma unroll
         for (int k = 0; k < kPairItems; ++k) c[k] = i0 + k < n ? pair_count[i0 + k] : 0u;
     }
+    if (pair_z) {
+#pragma unroll
+        for (int k = 0; k < kPairItems; ++k)
+            if (i0 + k < n && pair_z[i0 + k] == kNoDepth) c[k] = 0u;
+    }
 }
 
 // Also clears the tile counts.
-__global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_t* pair_count, long long n,
-                                                                   uint2* sums, uint32_t* tile_count, long long n_counts) {
+__global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_t* pair_count, const uint32_t* pair_z,
+                                                                   long long n, uint2* sums, uint32_t* tile_count,
+                                                                   long long n_counts) {
     __shared__ uint2 wave_tot[kPairThreads / 64];
     const long long g = (long long)blockIdx.x * kPairThreads + threadIdx.x;
     for (long long e = g; e < n_counts; e += (long long)gridDim.x * kPairThreads) tile_count[e] = 0u;
     uint32_t c[kPairItems];
-    load_counts(pair_count, n, g * kPairItems, c);
+    load_counts(pair_count, pair_z, n, g * kPairItems, c);
     uint2 v = make_uint2(0u, 0u), total;
 #pragma unroll
     for (int k = 0; k < kPairItems; ++k) {
@@ -308,8 +316,8 @@ __global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t* pair_count, long long n,
-                                                                  const uint2* sums, long long capacity,
+__global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t* pair_count, const uint32_t* pair_z,
+                                                                  long long n, const uint2* sums, long long capacity,
                                                                   uint32_t* which, uint32_t* out,
                                                                   uint32_t* block_first, uint32_t* counters) {
     __shared__ uint2 wave_tot[kPairThreads / 64];
@@ -321,7 +329,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t
     block_inclusive2(pre, wave_tot, before);
     const long long i0 = ((long long)blockIdx.x * kPairThreads + threadIdx.x) * kPairItems;
     uint32_t c[kPairItems];
-    load_counts(pair_count, n, i0, c);
+    load_counts(pair_count, pair_z, n, i0, c);
     uint2 v = make_uint2(0u, 0u);
 #pragma unroll
     for (int k = 0; k < kPairItems; ++k) {
@@ -608,9 +616,9 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
     for (uint32_t c0 = 0; c0 < n; c0 += kTileSortLds) {
         const uint32_t len = n - c0 < (uint32_t)kTileSortLds ? n - c0 : kTileSortLds;
         for (uint32_t i = t; i - lane < len; i += kTileSortThreads) {  // wave-uniform
-            // the last run's fillers are distinct and above every key
-            const uint32_t q = i < len ? qa[s + c0 + i] : i;
-            const uint32_t z = i < len ? pair_z[q] : 0xFFFFFFC0u + (uint32_t)lane;
+            // the last run's fillers are distinct and above every key, whose id is below 2^31
+            const uint32_t q = i < len ? qa[s + c0 + i] : 0xFFFFFFC0u + (uint32_t)lane;
+            const uint32_t z = i < len ? pair_z[q] : 0xFFFFFFFFu;
             const u64 key = ((u64)z << 32) | q;
             // ranks by the depth bits alone, four to an LDS read; lanes of equal depth find another's
             // entry in their place, and then the run is ranked by (depth, id)
@@ -624,6 +632,7 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint3
                 const uint4 v = reinterpret_cast<const uint4*>(rz)[j];
                 rank += (v.x < z ? 1 : 0) + (v.y < z ? 1 : 0) + (v.z < z ? 1 : 0) + (v.w < z ? 1 : 0);
             }
+            if (i >= len) rank = lane;
             wave_sync();
             run[rank] = key;
             wave_sync();
@@ -719,11 +728,12 @@ static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
     const int n_tiles = a.vt.tile_base[a.vt.n_views];
     const unsigned pgrid = (unsigned)((a.n_pairs + kPairBlock - 1) / kPairBlock);
     uint2* sums = reinterpret_cast<uint2*>(a.depth_keys[0]);
+    const uint32_t* const z = a.given_depths ? a.pair_z : nullptr;
     uint32_t* const count = a.tile_count;
     uint32_t* const base = a.tile_count + (size_t)kTileCounts * n_tiles;
-    hipLaunchKernelGGL(pair_reduce_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, a.n_pairs, sums,
+    hipLaunchKernelGGL(pair_reduce_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
                        count, (long long)kTileCounts * n_tiles);
-    hipLaunchKernelGGL(pair_apply_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, a.n_pairs, sums,
+    hipLaunchKernelGGL(pair_apply_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
                        a.capacity, a.depth_vals[0], a.emit_off, a.block_first, a.counters);
     const unsigned egrid = (unsigned)((a.capacity + kEmitSlots - 1) / kEmitSlots);
     uint32_t* const tk = a.tile_keys[0];

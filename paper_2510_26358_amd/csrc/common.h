@@ -483,6 +483,7 @@ struct BinArgs {
     uint32_t* counters;
     long long n_pairs;
     long long capacity;
+    bool given_depths;       // pair_z comes from given records: any bits, also kNoDepth where pair_count is not 0
     uint32_t* depth_keys[2]; // [n_pairs]
     uint32_t* depth_vals[2];
     uint32_t* emit_off;      // [n_pairs] scan of tile counts in depth order
