@@ -32,6 +32,11 @@ namespace ags {
 // every atomic (one 960 x 600 view over 300k Gaussians, one count: 66 us, eight 29, sixteen 20; without
 // counts 8).
 constexpr int kEmitThreads = 256;
+constexpr int kEmitTogether = 8;  // lanes of one tile that share an addition
+
+__device__ __forceinline__ uint32_t lanes_before(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
 template <bool RANK>
 __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const float* records,
@@ -150,7 +155,27 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const 
         const uint32_t tile = hit ? s_first[lo] + row * (wp >> 16) + col : n_tiles;
         tile_keys[k] = tile;
         tile_vals[k] = s_q[lo];
-        if (RANK && hit) tile_rank[k] = atomicAdd(tile_count + (size_t)(blockIdx.x % kTileCounts) * n_tiles + tile, 1u);
+        if (RANK && hit) {
+            // lanes of one tile add together where many meet (a far view's Gaussians in a few tiles: 300k in
+            // one tile 287 -> 12 us)
+            uint32_t* const count = tile_count + (size_t)(blockIdx.x % kTileCounts) * n_tiles;
+            unsigned long long left = __builtin_amdgcn_ballot_w64(true);
+            uint32_t rank = 0;
+            for (;;) {
+                const int lead = __builtin_ctzll(left);
+                const uint32_t lead_tile = (uint32_t)__builtin_amdgcn_readlane((int)tile, lead);
+                const unsigned long long same = __builtin_amdgcn_ballot_w64(tile == lead_tile) & left;
+                if (__popcll(same) < kEmitTogether) break;
+                uint32_t at = 0;
+                if (__lane_id() == lead) at = atomicAdd(count + lead_tile, (uint32_t)__popcll(same));
+                at = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
+                if (tile == lead_tile) rank = at + lanes_before(same);
+                left &= ~same;
+                if (left == 0ull) break;
+            }
+            if ((left >> __lane_id()) & 1ull) rank = atomicAdd(count + tile, 1u);
+            tile_rank[k] = rank;
+        }
     }
 }
 
@@ -234,8 +259,8 @@ __global__ __launch_bounds__(kWorkThreads) void work_list_kernel(const uint32_t*
 // ------------------------------------------------------------------------- per-tile sort
 //
 // The other way to the same lists, for launches whose lists are short: the pairs are emitted in pair
-// order, each intersection takes its place in its tile by a counter, and one workgroup a tile sorts the
-// tile's list by (depth bits, pair id).  Six launches instead of 23, of which none reads more than a few
+// order, each intersection takes its place in its tile by a counter, and each tile's list is sorted by (depth
+// bits, pair id).  Six launches instead of 23 (seven where lists may be long), of which none reads more than a few
 // megabytes: a launch costs about 4.5 us however little it does, so the two radix sorts cost about
 // 170 us of a 300k-Gaussian single view's step and 60 us of one over 4k.
 //
@@ -297,12 +322,13 @@ __device__ __forceinline__ void load_counts(const uint32_t* pair_count, const ui
     }
 }
 
-// Also clears the tile counts.
+// Also clears the tile counts and the number of segments.
 __global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_t* pair_count, const uint32_t* pair_z,
                                                                    long long n, uint2* sums, uint32_t* tile_count,
-                                                                   long long n_counts) {
+                                                                   long long n_counts, uint2* segs) {
     __shared__ uint2 wave_tot[kPairThreads / 64];
     const long long g = (long long)blockIdx.x * kPairThreads + threadIdx.x;
+    if (g == 0) segs[0] = make_uint2(0u, 0u);
     for (long long e = g; e < n_counts; e += (long long)gridDim.x * kPairThreads) tile_count[e] = 0u;
     uint32_t c[kPairItems];
     load_counts(pair_count, pair_z, n, g * kPairItems, c);
@@ -360,12 +386,29 @@ __global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t
     }
 }
 
+constexpr uint32_t kTileSortMost = 2048;  // entries that a workgroup sorts in LDS: 16 KB
+constexpr uint32_t kTileSortMerge = kTileSortMost / 2;  // the same by merges, which alternate between two buffers
+
+// A longer list is sorted in segments; one of more than kRunsFrom first in runs of kTileSortMerge.  Entries of a
+// segment on average: few enough that hardly one is over kTileSortMost, as an uneven sample makes them, since a
+// second reading of the list by one segment is waited for (lists of 300k, read: 232 us by 512, 424 by 1024).
+constexpr uint32_t kRunsFrom = 5u << 16;
+constexpr uint32_t kSegRead = 512, kSegSearch = 1024;
+__device__ __forceinline__ uint32_t tile_segments(uint32_t n) {
+    const uint32_t per = n > kRunsFrom ? kSegSearch : kSegRead;
+    return (n + per - 1) / per;
+}
+// Segments that a launch can have: the lists' entries are at most `capacity`, and each list has one more at most.
+long long tile_sort_segments(long long capacity) { return capacity / kSegRead + capacity / kTileSortMost; }
+static_assert(kSegSearch == kTileSortMerge, "a run for each segment");
+
 // The tile counts to the tiles' ranges, the first place of each (tile, count) and the list total
-// (workgroups 8 and up, 1024 tiles each, adding up the tiles before their own), and the raster work order
+// (workgroups 8 and up, 1024 tiles each, adding up the tiles before their own), the segments of the long lists
+// (segs, whose count was cleared before), and the raster work order
 // (workgroups 0..7, from the counts alone, so that nobody waits).
 __global__ __launch_bounds__(kWorkThreads) void tile_scan_kernel(const uint32_t* tile_count, uint32_t* tile_base,
                                                                  uint32_t* ranges, int n_tiles, int n_slots,
-                                                                 uint32_t* work, uint32_t* counters) {
+                                                                 uint32_t* work, uint2* segs, uint32_t* counters) {
     auto length = [&](int tile) {
         uint32_t n = 0;
 #pragma unroll
@@ -406,6 +449,14 @@ __global__ __launch_bounds__(kWorkThreads) void tile_scan_kernel(const uint32_t*
         total += wave_tot[0][x] + wave_tot[1][x];
     }
     if (blockIdx.x == gridDim.x - 1 && t == 0) counters[CNT_LIVE] = total;
+    for (unsigned long long left = __builtin_amdgcn_ballot_w64(sum > kTileSortMost); left; left &= left - 1) {
+        const int lead = __builtin_ctzll(left);  // the wave writes a long list's segments
+        const uint32_t m = tile_segments((uint32_t)__builtin_amdgcn_readlane((int)sum, lead));
+        uint32_t at = 0;
+        if (lane == lead) at = 1 + atomicAdd(&segs[0].x, m);
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
+        for (uint32_t j = lane; j < m; j += 64) segs[at + j] = make_uint2((uint32_t)(tile - lane + lead), j);
+    }
     if (tile >= n_tiles) return;
     reinterpret_cast<uint2*>(ranges)[tile] = sum ? make_uint2(run, run + sum) : make_uint2(0u, 0u);
 #pragma unroll
@@ -438,24 +489,45 @@ __global__ __launch_bounds__(256) void place_kernel(const uint32_t* tile_keys, c
         if (t[j] < n_tiles) out[base[t[j]] + r[j]] = q[j];
 }
 
-// One workgroup sorts a tile's list by (depth bits, pair id), a strict order.
+// A tile's list sorted by (depth bits, pair id), a strict order: by one workgroup, or in segments by several.
 //
-// Up to kTileSortMost entries: by buckets of the depth bits between the list's least and greatest, then each
-// entry by its rank in its bucket, which holds a few; a chain of some ten dependent LDS accesses, where
+// Up to kTileSortMost entries in LDS: by buckets of the depth bits between the entries' least and greatest,
+// then each entry by its rank in its bucket, which holds a few; a chain of some ten dependent LDS accesses, where
 // merging takes a hundred for 1000 entries.  Where some bucket holds more than kBucketMost (equal depths, a far
-// outlier), and for the pieces of kTileSortLds entries of a longer list: runs of 64 by each element's
-// rank among its run, then merges in which an element's place is its index in its own run plus its rank in
-// the other (a binary search).  The pieces of a longer list are merged through global memory, between the
-// pairs of arrays (za, qa) and (zb, qb), ending in (zb, qb).  On entry the list is in qa; on exit its ids are
-// in qb and the tile's id in zb.  The workgroups follow the raster work order, the longest lists first.
+// outlier), kTileSortMerge entries at a time: runs of 64 by each element's rank among its run, then merges in
+// which an element's place is its index in its own run plus its rank in the other (a binary search).
 // One 960 x 600 view over 300k Gaussians (2280 lists, up to 1286 entries): 30 us by merges alone, 15
 // by buckets; three views over 600k 50 and 34.
+//
+// A longer list is cut into ranges of keys at the quantiles of a sample, which each of the list's workgroups takes
+// for itself.  A segment's workgroup picks the entries of its range and counts those before it, which is where
+// its own begin, so nobody waits for anybody; a range of more entries than LDS holds is halved and its parts
+// done in turn.  Up to kRunsFrom entries the workgroup reads the whole list; of a list beyond, tile_runs_kernel has
+// sorted runs, and it searches each of them for the ends of its range.  Reading grows with the square of the list,
+// but up to the line it takes about as long as the radix sorts, and a launch without longer lists is not
+// delayed by the runs' kernel (2 us).  All binning, all Gaussians of a view in one tile, us:
+//   Gaussians                     5k   20k   50k  100k  200k  300k  400k  500k     1M
+//   one workgroup a list         197   954        6136
+//   reading the list              67    76    92   124   171   260   360   670
+//   searching runs               106    91    90    98   123   168   189   228    686
+//   radix sorts over all         115   120   151   215   220   222   228   232    266
 constexpr int kTileSortThreads = 256;
-constexpr int kTileSortLds = 1024;  // two buffers of 8 KB
-constexpr int kTileSortMost = 2 * kTileSortLds;
 constexpr int kTileSortItems = kTileSortMost / kTileSortThreads;
 constexpr int kBuckets = 1024, kBucketMost = 48;
 constexpr int kMergeItems = 4;  // searches a thread runs side by side
+// The thread's number, opaque to the optimiser: what follows from it is formed where it is used, instead of
+// being kept in registers around the loops of tile_sort_kernel.
+__device__ __forceinline__ int thread_number() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// A value that all lanes hold, in scalar registers.
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+    return ((unsigned long long)uniform32((uint32_t)(v >> 32)) << 32) | uniform32((uint32_t)v);
+}
 
 // Orders the wave's own LDS accesses (which complete in order) for the compiler.
 __device__ __forceinline__ void wave_sync() {
@@ -466,7 +538,7 @@ __device__ __forceinline__ void wave_sync() {
 // One level of merges of runs of R (a power of two) of n elements: element i to place(i's new place).
 template <typename Load, typename Place>
 __device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, Place place) {
-    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kMergeItems * kTileSortThreads) {
+    for (uint32_t i0 = thread_number(); i0 < n; i0 += kMergeItems * kTileSortThreads) {
         unsigned long long key[kMergeItems];
         uint32_t lo[kMergeItems], ps[kMergeItems], pl[kMergeItems];  // the other run: start, length
 #pragma unroll
@@ -493,17 +565,19 @@ __device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, P
     }
 }
 
-// Sorts len <= kTileSortMost entries (ids q[0 .. len)) into a; false, and a undefined, if a bucket is too full.
-__device__ __forceinline__ bool bucket_sort(const uint32_t* q, const uint32_t* pair_z, int len, unsigned long long* a,
+// Sorts len <= kTileSortMost entries (of the ids id_of(0 .. len), which may lie in a) into a; false, and a as it was,
+// if a bucket is too full.
+template <typename Id>
+__device__ __forceinline__ bool bucket_sort(Id id_of, const uint32_t* pair_z, int len, unsigned long long* a,
                                             uint32_t (&first)[kBuckets + 1], uint32_t (&part)[3][4]) {
     using u64 = unsigned long long;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int t = thread_number(), lane = t & 63, w = t >> 6;
     constexpr int BT = kBuckets / kTileSortThreads;
     uint32_t id[kTileSortItems], z[kTileSortItems], lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
     for (int k = 0; k < kTileSortItems; ++k) {
         const int i = t + k * kTileSortThreads;
-        if (i < len) id[k] = q[i];
+        if (i < len) id[k] = id_of(i);
     }
 #pragma unroll
     for (int k = 0; k < kTileSortItems; ++k) {
@@ -592,90 +666,262 @@ __device__ __forceinline__ bool bucket_sort(const uint32_t* q, const uint32_t* p
     return true;
 }
 
-__global__ __launch_bounds__(kTileSortThreads) void tile_sort_kernel(const uint32_t* pair_z, const uint32_t* ranges,
-                                                                     const uint32_t* work, uint32_t* za,
-                                                                     uint32_t* qa, uint32_t* zb, uint32_t* qb) {
+// Sorts len <= kTileSortMerge entries (of the ids id_of(0 .. len), which may lie in the upper half of buf) into
+// one of the halves of buf, and returns where that begins.
+template <typename Id>
+__device__ __forceinline__ uint32_t merge_sort(Id id_of, const uint32_t* pair_z, uint32_t len,
+                                               unsigned long long* buf) {
     using u64 = unsigned long long;
-    __shared__ __align__(16) u64 buf[2][kTileSortLds];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const uint32_t tile = work[blockIdx.x];
-    if (tile == kNoTile) return;
+    const int t = thread_number(), lane = t & 63;
+    for (uint32_t i = t; i - lane < len; i += kTileSortThreads) {  // wave-uniform
+        // the last run's fillers are distinct and above every key, whose id is below 2^31
+        const uint32_t q = i < len ? id_of(i) : 0xFFFFFFC0u + (uint32_t)lane;
+        const uint32_t z = i < len ? pair_z[q] : 0xFFFFFFFFu;
+        const u64 key = ((u64)z << 32) | q;
+        // ranks by the depth bits alone, four to an LDS read; lanes of equal depth find another's
+        // entry in their place, and then the run is ranked by (depth, id)
+        u64* const run = buf + (i - lane);
+        uint32_t* const rz = reinterpret_cast<uint32_t*>(run);
+        rz[lane] = z;
+        wave_sync();
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < 16; ++j) {
+            const uint4 v = reinterpret_cast<const uint4*>(rz)[j];
+            rank += (v.x < z ? 1 : 0) + (v.y < z ? 1 : 0) + (v.z < z ? 1 : 0) + (v.w < z ? 1 : 0);
+        }
+        if (i >= len) rank = lane;
+        wave_sync();
+        run[rank] = key;
+        wave_sync();
+        if (__builtin_amdgcn_ballot_w64(run[rank] != key) != 0ull) {
+            wave_sync();
+            run[lane] = key;
+            wave_sync();
+            rank = 0;
+            for (int j = 0; j < 64; ++j) rank += run[j] < key ? 1 : 0;
+            wave_sync();
+            run[rank] = key;
+        }
+    }
+    __syncthreads();
+    uint32_t from = 0;
+    for (uint32_t R = 64; R < len; R <<= 1, from ^= kTileSortMerge) {
+        const u64* const in = buf + from;
+        u64* const out = buf + (from ^ kTileSortMerge);
+        merge_level((len + 63) & ~63u, R, [&](uint32_t i) { return in[i]; },
+                    [&](uint32_t p, u64 key) { out[p] = key; });
+        __syncthreads();
+    }
+    return from;
+}
+
+// Minimum, maximum and sum over the workgroup.
+__device__ __forceinline__ void block_range(unsigned long long& least, unsigned long long& most, uint32_t& sum,
+                                            unsigned long long (&part)[3][4]) {
+    using u64 = unsigned long long;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const u64 x = __shfl_xor(least, o, 64), y = __shfl_xor(most, o, 64);
+        least = x < least ? x : least;
+        most = y > most ? y : most;
+        sum += (uint32_t)__shfl_xor((int)sum, o, 64);
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        part[0][w] = least;
+        part[1][w] = most;
+        part[2][w] = sum;
+    }
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int x = 0; x < kTileSortThreads / 64; ++x) {
+        least = part[0][x] < least ? part[0][x] : least;
+        most = part[1][x] > most ? part[1][x] : most;
+        sum += (uint32_t)part[2][x];
+    }
+}
+
+// The lists of more than kRunsFrom entries in sorted runs of kTileSortMerge, to the same places of `runs`.
+__global__ __launch_bounds__(kTileSortThreads) void tile_runs_kernel(const uint32_t* pair_z, const uint32_t* ranges,
+                                                                     const uint2* segs, const uint32_t* list,
+                                                                     uint32_t* runs) {
+    __shared__ __align__(16) unsigned long long buf[kTileSortMost];
+    __shared__ uint32_t first[kBuckets + 1], part[3][4];
+    for (uint32_t x = blockIdx.x; x < segs[0].x; x += gridDim.x) {
+        const uint2 job = segs[1 + x];
+        const uint2 se = reinterpret_cast<const uint2*>(ranges)[job.x];
+        const uint32_t n = se.y - se.x, at = job.y * kTileSortMerge;  // as many runs as segments
+        if (n <= kRunsFrom) continue;
+        const uint32_t len = min(n - at, kTileSortMerge);
+        const uint32_t* const q = list + se.x + at;
+        auto id_of = [&](uint32_t i) { return q[i]; };
+        uint32_t from = 0;
+        if (!bucket_sort(id_of, pair_z, (int)len, buf, first, part)) from = merge_sort(id_of, pair_z, len, buf);
+        for (uint32_t i = threadIdx.x; i < len; i += kTileSortThreads) runs[se.x + at + i] = (uint32_t)buf[from + i];
+        __syncthreads();
+    }
+}
+
+// Workgroups 0 .. n_work - 1: the lists of up to kTileSortMost entries, in the raster work order, the longest
+// first; the others, last because most launches have none of them: the segments in segs (their number in
+// segs[0].x, then (tile, segment)).  A tile's ids in `list` go to qb in order, the tile's id to tiles; runs: null
+// where no list can be longer than kRunsFrom.  Seven waves a SIMD by the LDS: the registers are held to those,
+// which costs the segments a spill (of 96 registers; without, all lists of a 300k view take 4 us longer).
+__global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
+    const uint32_t* pair_z, const uint32_t* ranges, const uint32_t* work, const uint2* segs, uint32_t n_work,
+    const uint32_t* list, const uint32_t* runs, uint32_t* tiles, uint32_t* qb) {
+    using u64 = unsigned long long;
+    __shared__ __align__(16) u64 buf[kTileSortMost];
+    __shared__ uint32_t first[kBuckets + 1], part[3][4];
+    const bool segment = blockIdx.x >= n_work;
+    uint2 job = make_uint2(0u, 0u);
+    if (segment) {
+        if (blockIdx.x - n_work >= segs[0].x) return;
+        job = segs[1 + blockIdx.x - n_work];
+    } else {
+        job.x = work[blockIdx.x];
+        if (job.x == kNoTile) return;
+    }
+    const uint32_t tile = job.x;
     const uint2 se = reinterpret_cast<const uint2*>(ranges)[tile];
     const uint32_t n = se.y - se.x, s = se.x;
-    if (n == 0u) return;
-    __shared__ uint32_t first[kBuckets + 1], part[3][4];
-    if (n <= (uint32_t)kTileSortMost && bucket_sort(qa + s, pair_z, (int)n, buf[0], first, part)) {
-        for (uint32_t i = t; i < n; i += kTileSortThreads) {
-            zb[s + i] = tile;
-            qb[s + i] = (uint32_t)buf[0][i];
+    if (n == 0u || (!segment && n > kTileSortMost)) return;
+    const uint32_t* const q = list + s;
+    if (!segment && bucket_sort([&](int i) { return q[i]; }, pair_z, (int)n, buf, first, part)) {
+        for (uint32_t i = threadIdx.x; i < n; i += kTileSortThreads) {
+            tiles[s + i] = tile;
+            qb[s + i] = (uint32_t)buf[i];
         }
         return;
     }
-    int levels = 0;  // merges through global memory
-    while (((uint32_t)kTileSortLds << levels) < n) ++levels;
-    for (uint32_t c0 = 0; c0 < n; c0 += kTileSortLds) {
-        const uint32_t len = n - c0 < (uint32_t)kTileSortLds ? n - c0 : kTileSortLds;
-        for (uint32_t i = t; i - lane < len; i += kTileSortThreads) {  // wave-uniform
-            // the last run's fillers are distinct and above every key, whose id is below 2^31
-            const uint32_t q = i < len ? qa[s + c0 + i] : 0xFFFFFFC0u + (uint32_t)lane;
-            const uint32_t z = i < len ? pair_z[q] : 0xFFFFFFFFu;
-            const u64 key = ((u64)z << 32) | q;
-            // ranks by the depth bits alone, four to an LDS read; lanes of equal depth find another's
-            // entry in their place, and then the run is ranked by (depth, id)
-            u64* const run = buf[0] + (i - lane);
-            uint32_t* const rz = reinterpret_cast<uint32_t*>(run);
-            rz[lane] = z;
-            wave_sync();
-            int rank = 0;
-#pragma unroll 4
-            for (int j = 0; j < 16; ++j) {
-                const uint4 v = reinterpret_cast<const uint4*>(rz)[j];
-                rank += (v.x < z ? 1 : 0) + (v.y < z ? 1 : 0) + (v.z < z ? 1 : 0) + (v.w < z ? 1 : 0);
-            }
-            if (i >= len) rank = lane;
-            wave_sync();
-            run[rank] = key;
-            wave_sync();
-            if (__builtin_amdgcn_ballot_w64(run[rank] != key) != 0ull) {
-                wave_sync();
-                run[lane] = key;
-                wave_sync();
-                rank = 0;
-                for (int j = 0; j < 64; ++j) rank += run[j] < key ? 1 : 0;
-                wave_sync();
-                run[rank] = key;
-            }
-        }
+    // A sample of the list gives a segment its keys [lo, end); then the entries from lo up to hi, which is end
+    // unless they are too many, are picked and sorted, until they are done up to the end.
+    __shared__ u64 range_part[3][4];
+    __shared__ uint32_t n_in;
+    auto key_of = [&](uint32_t id) { return ((u64)pair_z[id] << 32) | id; };
+    uint32_t* const picked = reinterpret_cast<uint32_t*>(buf + kTileSortMerge);  // up to kTileSortMost ids
+    u64 lo = 0ull, end = ~0ull, hi = end;
+    uint32_t limit = segment ? kTileSortMost : kTileSortMerge;
+    bool sampled = !segment;
+    for (;;) {
+        const int t = thread_number();
         __syncthreads();
-        int cur = 0;
-        for (uint32_t R = 64; R < len; R <<= 1, cur ^= 1) {
-            const u64* const in = buf[cur];
-            u64* const out = buf[cur ^ 1];
-            merge_level((len + 63) & ~63u, R, [&](uint32_t i) { return in[i]; },
-                        [&](uint32_t p, u64 key) { out[p] = key; });
+        uint32_t c = limit, below = 0u;
+        if (!sampled) {
+            for (uint32_t i = t; i < c; i += kTileSortThreads) picked[i] = q[(uint32_t)((u64)i * n / c)];
             __syncthreads();
+        } else {
+            if (t == 0) n_in = 0u;
+            __syncthreads();
+            u64 least = ~0ull, most = 0ull;
+            if (runs && n > kRunsFrom) {
+                // each run's entries of [lo, hi) lie together: two binary searches a run, side by side
+                const uint32_t* const r = runs + s;
+                const uint32_t n_runs = (n + kTileSortMerge - 1) / kTileSortMerge;
+                for (uint32_t i0 = t; i0 < n_runs; i0 += kMergeItems * kTileSortThreads) {
+                    uint32_t from[kMergeItems], first_in[kMergeItems], first_out[kMergeItems], len[kMergeItems];
+#pragma unroll
+                    for (int k = 0; k < kMergeItems; ++k) {
+                        const uint32_t i = i0 + k * kTileSortThreads;
+                        from[k] = i * kTileSortMerge;
+                        len[k] = i < n_runs ? (n - from[k] < kTileSortMerge ? n - from[k] : kTileSortMerge) : 0u;
+                        first_in[k] = first_out[k] = 0u;
+                    }
+                    for (uint32_t step = kTileSortMerge; step > 0; step >>= 1) {
+#pragma unroll
+                        for (int k = 0; k < kMergeItems; ++k) {
+                            const uint32_t x = first_in[k] + step, y = first_out[k] + step;
+                            if (x <= len[k] && key_of(r[from[k] + x - 1]) < lo) first_in[k] = x;
+                            if (y <= len[k] && key_of(r[from[k] + y - 1]) < hi) first_out[k] = y;
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < kMergeItems; ++k) {
+                        below += first_in[k];
+                        if (first_in[k] == first_out[k]) continue;
+                        const u64 x = key_of(r[from[k] + first_in[k]]), y = key_of(r[from[k] + first_out[k] - 1]);
+                        least = x < least ? x : least;
+                        most = y > most ? y : most;
+                        const uint32_t k_in = first_out[k] - first_in[k], p = atomicAdd(&n_in, k_in);
+                        for (uint32_t e = 0; e < k_in && p + e < limit; ++e)
+                            picked[p + e] = r[from[k] + first_in[k] + e];
+                    }
+                }
+            } else {
+                // most entries are told by their depth bits alone; the next ids are asked for behind the depths
+                const uint32_t z_lo = (uint32_t)(lo >> 32), z_hi = (uint32_t)((hi - 1) >> 32);
+                constexpr int U = 8;
+                uint32_t id[U];
+                auto load = [&](uint32_t i0) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t i = i0 + u * kTileSortThreads;
+                        id[u] = i < n ? q[i] : 0xFFFFFFFFu;
+                    }
+                };
+                load(t);
+                for (uint32_t i0 = t; i0 - t < n; i0 += U * kTileSortThreads) {
+                    uint32_t z[U], now[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        now[u] = id[u];
+                        z[u] = pair_z[now[u] == 0xFFFFFFFFu ? 0u : now[u]];
+                    }
+                    load(i0 + U * kTileSortThreads);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (now[u] == 0xFFFFFFFFu) z[u] = 0xFFFFFFFFu;  // past the list: not below any end
+                        below += z[u] < z_lo ? 1u : 0u;
+                        const bool near = z[u] >= z_lo && z[u] <= z_hi;
+                        if (__builtin_amdgcn_ballot_w64(near) == 0ull) continue;
+                        const u64 key = ((u64)z[u] << 32) | now[u];
+                        if (near && key < lo) ++below;
+                        if (near && key >= lo && key < hi) {
+                            least = key < least ? key : least;
+                            most = key > most ? key : most;
+                            const uint32_t p = atomicAdd(&n_in, 1u);
+                            if (p < limit) picked[p] = now[u];
+                        }
+                    }
+                }
+            }
+            block_range(least, most, below, range_part);
+            least = uniform64(least);
+            most = uniform64(most);
+            below = uniform32(below);
+            c = uniform32(n_in);
+            if (c > limit) {  // of at least two distinct keys
+                hi = least + (most - least) / 2 + 1;
+                continue;
+            }
         }
-        uint32_t* const zo = levels & 1 ? za : zb;
-        uint32_t* const qo = levels & 1 ? qa : qb;
-        for (uint32_t i = t; i < len; i += kTileSortThreads) {
-            const u64 v = buf[cur][i];
-            zo[s + c0 + i] = levels ? (uint32_t)(v >> 32) : tile;
-            qo[s + c0 + i] = (uint32_t)v;
+        auto id_of = [&](uint32_t i) { return picked[i]; };
+        uint32_t from = 0;
+        if (limit == kTileSortMost) {
+            if (!bucket_sort(id_of, pair_z, (int)c, buf, first, part)) {
+                limit = kTileSortMerge;
+                continue;
+            }
+        } else {
+            from = merge_sort(id_of, pair_z, c, buf);
         }
-        __syncthreads();
-    }
-    for (int l = levels; l > 0; --l) {  // from (za, qa) when l is odd
-        const uint32_t* const zi = (l & 1 ? za : zb) + s;
-        const uint32_t* const qi = (l & 1 ? qa : qb) + s;
-        uint32_t* const zo = (l & 1 ? zb : za) + s;
-        uint32_t* const qo = (l & 1 ? qb : qa) + s;
-        merge_level(n, (uint32_t)kTileSortLds << (levels - l),
-                    [&](uint32_t i) { return ((u64)zi[i] << 32) | qi[i]; },
-                    [&](uint32_t p, u64 key) {
-                        zo[p] = l == 1 ? tile : (uint32_t)(key >> 32);
-                        qo[p] = (uint32_t)key;
-                    });
-        __syncthreads();
+        if (!sampled) {
+            const uint32_t m = tile_segments(n);
+            if (job.y > 0) lo = uniform64(buf[from + job.y * c / m]);
+            if (job.y + 1 < m) end = uniform64(buf[from + (job.y + 1) * c / m]);
+            hi = end;
+            sampled = true;
+            continue;
+        }
+        for (uint32_t i = t; i < c; i += kTileSortThreads) {
+            tiles[s + below + i] = tile;
+            qb[s + below + i] = (uint32_t)buf[from + i];
+        }
+        if (hi == end) return;
+        lo = hi;
+        hi = end;
     }
 }
 
@@ -706,22 +952,27 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
 }
 
 // Which way a launch takes: the lists sorted tile by tile, or two radix sorts over all.  Tile by tile
-// is six launches (about 4.5 us each however little they do) against 23, but its atomics, scattered
-// places and merges cost more per intersection.  Binning of one 300k-Gaussian view (0.5M
+// is six or seven launches (about 4.5 us each however little they do) against 23, but its atomics, scattered
+// places and sorts cost more per intersection.  Binning of one 300k-Gaussian view (0.5M
 // intersections) 190 us by radix sorts, 51 tile by tile; three views over 600k (2.4M) 208 and 158; four
-// over 1M (7.5M) 304 and 361.  And one workgroup sorts a list, which beyond a few thousand entries takes
-// longer than all the radix passes (a piece of 1024 about 7 us, a merge level of 4096 about 30): no list can
-// be longer than its view's Gaussian range, or the capacity leaves at most 512 entries a tile on average.
-constexpr long long kTileSortCapacity = 1ll << 22, kTileSortLongest = 4096, kTileSortMean = 512;
+// over 1M (7.5M) 304 and 361.  Long lists cost it the most (see the table at bucket_sort): lists are at most 4096
+// entries long because no view has more Gaussians, or the capacity leaves 512 a tile on average, which bounds
+// no single list, and no view has more than 2^20 Gaussians.  If those all lie in one tile it is as fast as the radix
+// sorts up to 500k, at 1M 686 us and 266.
+constexpr long long kTileSortCapacity = 1ll << 22, kTileSortShort = 4096, kTileSortMean = 512;
+constexpr long long kTileSortLongest = 1ll << 20;
+// No list is longer than its view's Gaussian range, or than the capacity.
+static long long longest_list(const ViewTable& vt, long long capacity) {
+    long long n = 0;
+    for (int b = 0; b < vt.n_views; ++b) n = max(n, (long long)vt.g_end[b] - vt.g_begin[b]);
+    return min(n, capacity);
+}
+
 bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity) {
     const long long n_tiles = vt.tile_base[vt.n_views];
     if (n_pairs <= 0 || n_tiles <= 0 || capacity <= 0 || capacity > kTileSortCapacity) return false;
-    long long longest = 0;
-    for (int b = 0; b < vt.n_views; ++b) {
-        const long long n = vt.g_end[b] - vt.g_begin[b];
-        longest = n > longest ? n : longest;
-    }
-    return longest <= kTileSortLongest || capacity <= kTileSortLongest || capacity <= kTileSortMean * n_tiles;
+    const long long longest = longest_list(vt, capacity);
+    return longest <= kTileSortShort || (longest <= kTileSortLongest && capacity <= kTileSortMean * n_tiles);
 }
 
 static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
@@ -731,8 +982,9 @@ static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
     const uint32_t* const z = a.given_depths ? a.pair_z : nullptr;
     uint32_t* const count = a.tile_count;
     uint32_t* const base = a.tile_count + (size_t)kTileCounts * n_tiles;
+    uint2* const segs = reinterpret_cast<uint2*>(base + (size_t)kTileCounts * n_tiles);
     hipLaunchKernelGGL(pair_reduce_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
-                       count, (long long)kTileCounts * n_tiles);
+                       count, (long long)kTileCounts * n_tiles, segs);
     hipLaunchKernelGGL(pair_apply_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
                        a.capacity, a.depth_vals[0], a.emit_off, a.block_first, a.counters);
     const unsigned egrid = (unsigned)((a.capacity + kEmitSlots - 1) / kEmitSlots);
@@ -744,11 +996,17 @@ static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
                        a.emit_off, a.block_first, a.counters, a.capacity, tk, tv, tr, count, a.ranges);
     const unsigned tgrid = 8 + (unsigned)((n_tiles + kWorkThreads - 1) / kWorkThreads);
     hipLaunchKernelGGL(tile_scan_kernel, dim3(tgrid), dim3(kWorkThreads), 0, s, count, base, a.ranges, n_tiles,
-                       raster_blocks(a.vt), a.work, a.counters);
+                       raster_blocks(a.vt), a.work, segs, a.counters);
     hipLaunchKernelGGL(place_kernel, dim3(egrid), dim3(256), 0, s, tk, tv, tr, base, a.counters, a.capacity,
                        (uint32_t)n_tiles, list);
-    hipLaunchKernelGGL(tile_sort_kernel, dim3((unsigned)raster_blocks(a.vt)), dim3(kTileSortThreads), 0, s, a.pair_z,
-                       a.ranges, a.work, tr, list, tk, tv);
+    const uint32_t seg_grid = (uint32_t)tile_sort_segments(a.capacity);
+    uint32_t* const runs = longest_list(a.vt, a.capacity) > kRunsFrom ? tr : nullptr;
+    if (runs)
+        hipLaunchKernelGGL(tile_runs_kernel, dim3(min(seg_grid, 1024u)), dim3(kTileSortThreads), 0, s, a.pair_z,
+                           a.ranges, segs, list, runs);
+    const uint32_t n_work = (uint32_t)raster_blocks(a.vt);
+    hipLaunchKernelGGL(tile_sort_kernel, dim3(n_work + seg_grid), dim3(kTileSortThreads), 0, s, a.pair_z, a.ranges,
+                       a.work, segs, n_work, list, runs, tk, tv);
     return (int)hipGetLastError();
 }
 
