@@ -322,7 +322,8 @@ __device__ __forceinline__ void load_counts(const uint32_t* pair_count, const ui
     }
 }
 
-// Also clears the tile counts and the number of segments.
+// Also clears the tile counts and the number of segments, with workgroups of its own where the tiles outnumber the
+// pairs (1000 pairs, 32,400 tiles: all binning 119 -> 67 us).
 __global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_t* pair_count, const uint32_t* pair_z,
                                                                    long long n, uint2* sums, uint32_t* tile_count,
                                                                    long long n_counts, uint2* segs) {
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_reduce_kernel(const uint32_
         v.y += c[k] ? 1u : 0u;
     }
     block_inclusive2(v, wave_tot, total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+    if (threadIdx.x == 0 && (long long)blockIdx.x * kPairBlock < n) sums[blockIdx.x] = total;
 }
 
 __global__ __launch_bounds__(kPairThreads) void pair_apply_kernel(const uint32_t* pair_count, const uint32_t* pair_z,
@@ -958,9 +959,12 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
 // over 1M (7.5M) 304 and 361.  Long lists cost it the most (see the table at bucket_sort): lists are at most 4096
 // entries long because no view has more Gaussians, or the capacity leaves 512 a tile on average, which bounds
 // no single list, and no view has more than 2^20 Gaussians.  If those all lie in one tile it is as fast as the radix
-// sorts up to 500k, at 1M 686 us and 266.
+// sorts up to 500k, at 1M 686 us and 266.  Its scans, of 2048 pairs or 1024 tiles a workgroup, each of which adds up the
+// sums of those before it, grow with the square of their number: per tile and by radix sorts, 30k Gaussians in
+// 32,400 tiles 109 and 124 us, 65,536 tiles 151 and 143, 129,600 tiles 233 and 161 (200k: 138 and 222, 213 and 240, 369
+// and 251); 4.2M pairs of which 400k are visible 234 and 252, 8.4M 395 and 371, 34M 1514 and 1099.
 constexpr long long kTileSortCapacity = 1ll << 22, kTileSortShort = 4096, kTileSortMean = 512;
-constexpr long long kTileSortLongest = 1ll << 20;
+constexpr long long kTileSortLongest = 1ll << 20, kTileSortTiles = 1ll << 16, kTileSortPairs = 1ll << 23;
 // No list is longer than its view's Gaussian range, or than the capacity.
 static long long longest_list(const ViewTable& vt, long long capacity) {
     long long n = 0;
@@ -970,7 +974,8 @@ static long long longest_list(const ViewTable& vt, long long capacity) {
 
 bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity) {
     const long long n_tiles = vt.tile_base[vt.n_views];
-    if (n_pairs <= 0 || n_tiles <= 0 || capacity <= 0 || capacity > kTileSortCapacity) return false;
+    if (n_pairs <= 0 || n_pairs > kTileSortPairs || n_tiles <= 0 || n_tiles > kTileSortTiles) return false;
+    if (capacity <= 0 || capacity > kTileSortCapacity) return false;
     const long long longest = longest_list(vt, capacity);
     return longest <= kTileSortShort || (longest <= kTileSortLongest && capacity <= kTileSortMean * n_tiles);
 }
@@ -983,8 +988,10 @@ static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {
     uint32_t* const count = a.tile_count;
     uint32_t* const base = a.tile_count + (size_t)kTileCounts * n_tiles;
     uint2* const segs = reinterpret_cast<uint2*>(base + (size_t)kTileCounts * n_tiles);
-    hipLaunchKernelGGL(pair_reduce_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
-                       count, (long long)kTileCounts * n_tiles, segs);
+    const long long n_counts = (long long)kTileCounts * n_tiles;
+    const unsigned clear_grid = (unsigned)((n_counts + 16 * kPairThreads - 1) / (16 * kPairThreads));
+    hipLaunchKernelGGL(pair_reduce_kernel, dim3(max(pgrid, clear_grid)), dim3(kPairThreads), 0, s, a.pair_count, z,
+                       a.n_pairs, sums, count, n_counts, segs);
     hipLaunchKernelGGL(pair_apply_kernel, dim3(pgrid), dim3(kPairThreads), 0, s, a.pair_count, z, a.n_pairs, sums,
                        a.capacity, a.depth_vals[0], a.emit_off, a.block_first, a.counters);
     const unsigned egrid = (unsigned)((a.capacity + kEmitSlots - 1) / kEmitSlots);
