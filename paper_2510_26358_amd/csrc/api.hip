@@ -166,8 +166,7 @@ int build_layout(const ags_config* cfg, const ags_views* views, int n, long long
     L.f_rowtot = o; o = align_up(o + (size_t)sort_rowtot_entries() * 4);
     L.f_block_sums = o; o = align_up(o + (size_t)sb * 4);
     L.f_tile_count = o;
-    if (per_tile_sort(vt, L.Q, L.cap))
-        o = align_up(o + 2 * (size_t)kTileCounts * L.n_tiles * 4 + (1 + (size_t)tile_sort_segments(L.cap)) * 8);
+    o = align_up(o + tile_sort_bytes(L.n_tiles, L.cap));
     L.f_total = o;
     o = 0;
     L.n_ssim = ssim_blocks(vt);

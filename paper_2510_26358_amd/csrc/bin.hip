@@ -32,6 +32,7 @@ namespace ags {
 // every atomic (one 960 x 600 view over 300k Gaussians, one count: 66 us, eight 29, sixteen 20; without
 // counts 8).
 constexpr int kEmitThreads = 256;
+constexpr int kTileCounts = 16;   // a multiple of the XCDs
 constexpr int kEmitTogether = 8;  // lanes of one tile that share an addition
 
 __device__ __forceinline__ uint32_t lanes_before(unsigned long long m) {
@@ -400,7 +401,7 @@ __device__ __forceinline__ uint32_t tile_segments(uint32_t n) {
     return (n + per - 1) / per;
 }
 // Segments that a launch can have: the lists' entries are at most `capacity`, and each list has one more at most.
-long long tile_sort_segments(long long capacity) { return capacity / kSegRead + capacity / kTileSortMost; }
+static long long tile_sort_segments(long long capacity) { return capacity / kSegRead + capacity / kTileSortMost; }
 static_assert(kSegSearch == kTileSortMerge, "a run for each segment");
 
 // The tile counts to the tiles' ranges, the first place of each (tile, count) and the list total
@@ -972,12 +973,19 @@ static long long longest_list(const ViewTable& vt, long long capacity) {
     return min(n, capacity);
 }
 
-bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity) {
+static bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity) {
     const long long n_tiles = vt.tile_base[vt.n_views];
     if (n_pairs <= 0 || n_pairs > kTileSortPairs || n_tiles <= 0 || n_tiles > kTileSortTiles) return false;
     if (capacity <= 0 || capacity > kTileSortCapacity) return false;
     const long long longest = longest_list(vt, capacity);
     return longest <= kTileSortShort || (longest <= kTileSortLongest && capacity <= kTileSortMean * n_tiles);
+}
+
+// Two sets of counts, then the segments.  Reserved for every launch, whichever way it takes: the workspace of a larger
+// capacity, view or map has room for a smaller one.
+size_t tile_sort_bytes(long long n_tiles, long long capacity) {
+    const size_t tiles = (size_t)min(n_tiles, kTileSortTiles), cap = (size_t)min(capacity, kTileSortCapacity);
+    return 2 * kTileCounts * tiles * sizeof(uint32_t) + (1 + (size_t)tile_sort_segments(cap)) * sizeof(uint2);
 }
 
 static int launch_binning_per_tile(BinArgs& a, hipStream_t s) {

@@ -487,7 +487,7 @@ struct BinArgs {
     uint32_t* depth_keys[2]; // [n_pairs]
     uint32_t* depth_vals[2];
     uint32_t* emit_off;      // [n_pairs] scan of tile counts in depth order
-    uint32_t* tile_count;    // [2 kTileCounts][n_tiles], then [1 + tile_sort_segments] pairs, where per_tile_sort
+    uint32_t* tile_count;    // tile_sort_bytes
     uint32_t* block_first;   // [capacity / kEmitSlots + 1] first depth-ordered pair of each emit workgroup
     uint32_t* tile_keys[2];  // [capacity]
     uint32_t* tile_vals[2];
@@ -502,10 +502,8 @@ struct BinArgs {
 void launch_count_from_records(const ViewTable& vt, const float* records, const uint8_t* valid,
                                long long n_pairs, uint32_t* pair_count, uint32_t* pair_z,
                                hipStream_t s);
-// Whether a launch sorts each tile's list by itself (see launch_binning); it then needs tile_count.
-bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capacity);
-constexpr int kTileCounts = 16;  // a multiple of the XCDs
-long long tile_sort_segments(long long capacity);
+// Scratch of the launches that sort each tile's list by itself (see launch_binning).
+size_t tile_sort_bytes(long long n_tiles, long long capacity);
 // Runs the depth sort (its first pass drops the pairs no tile receives), tile-count scan,
 // emission, tile sort and ranges.  Returns 0 or a HIP error.
 int launch_binning(BinArgs& a, hipStream_t s);
