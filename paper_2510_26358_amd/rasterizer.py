@@ -241,6 +241,18 @@ class Buffers:
         return int(self.view(self.sizes.off_counters, 5, torch.int32)[4].item())
 
 
+def first_capacity(views: ViewSpec) -> int:
+    """Intersections to make room for when nothing is known of a scene: one per two pixels, and two per (view,
+    Gaussian) pair as far as these stay below 2^26.
+
+    Scenes have 0.7 to 2.7 a pair, counting the culled ones, and an overflow costs a whole second forward (a
+    150k-Gaussian render of three views and its backward: 756 us with a guess by the pixels alone, 2 % too
+    small, 423 by the pairs).  An intersection takes 16 bytes: beyond 2^26 the pairs' share would be over 1 GiB,
+    most of it for culled pairs, and from 2^30 pairs more than the library takes."""
+    n_pairs = sum(e - b for b, e in zip(views.g_begin, views.g_end))
+    return max(1 << 16, views.n_pixels // 2, min(2 * n_pairs, 1 << 26))
+
+
 class Rasterizer:
     """A library context plus settings.  One instance per stream at a time."""
 
@@ -398,17 +410,13 @@ class Rasterizer:
         """Forward with automatic capacity growth (synchronises to read the counters).
         Returns (out, buffers).
 
-        Without a known capacity the first guess is two intersections per (view, Gaussian) pair,
-        at least one per two pixels: scenes have 0.7 to 2.7 a pair, counting the culled ones, and
-        an overflow costs a whole second forward (a 150k-Gaussian render of three views and its
-        backward: 756 us with a guess by the pixels alone, 2 % too small, 423 by the pairs)."""
+        Without a known capacity the first guess is first_capacity(views)."""
         if capacity:
             cap = capacity
         elif buf is not None:
             cap = buf.capacity
         else:
-            n_pairs = sum(e - b for b, e in zip(views.g_begin, views.g_end))
-            cap = max(1 << 16, views.n_pixels // 2, 2 * n_pairs)
+            cap = first_capacity(views)
         while True:
             if buf is None or buf.capacity < cap:
                 buf = self.buffers(views, params.n, params.sh_degree, cap)
