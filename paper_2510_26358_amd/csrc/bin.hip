@@ -157,24 +157,27 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(ViewTable vt, const 
         tile_keys[k] = tile;
         tile_vals[k] = s_q[lo];
         if (RANK && hit) {
-            // lanes of one tile add together where many meet (a far view's Gaussians in a few tiles: 300k in
-            // one tile 287 -> 12 us)
+            // Lanes of one tile add together where many meet (a far view's Gaussians in a few tiles: 300k in
+            // one tile 287 -> 12 us); the wave's additions are still one instruction, with one wait.
             uint32_t* const count = tile_count + (size_t)(blockIdx.x % kTileCounts) * n_tiles;
-            unsigned long long left = __builtin_amdgcn_ballot_w64(true);
-            uint32_t rank = 0;
-            for (;;) {
-                const int lead = __builtin_ctzll(left);
-                const uint32_t lead_tile = (uint32_t)__builtin_amdgcn_readlane((int)tile, lead);
-                const unsigned long long same = __builtin_amdgcn_ballot_w64(tile == lead_tile) & left;
+            const int self = __lane_id();
+            int lead = self;
+            uint32_t together = 1, before = 0;
+            for (unsigned long long left = __builtin_amdgcn_ballot_w64(true); left;) {
+                const int l = __builtin_ctzll(left);
+                const unsigned long long same =
+                    __builtin_amdgcn_ballot_w64(tile == (uint32_t)__builtin_amdgcn_readlane((int)tile, l)) & left;
                 if (__popcll(same) < kEmitTogether) break;
-                uint32_t at = 0;
-                if (__lane_id() == lead) at = atomicAdd(count + lead_tile, (uint32_t)__popcll(same));
-                at = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
-                if (tile == lead_tile) rank = at + lanes_before(same);
+                if ((same >> self) & 1ull) {
+                    lead = l;
+                    together = (uint32_t)__popcll(same);
+                    before = lanes_before(same);
+                }
                 left &= ~same;
-                if (left == 0ull) break;
             }
-            if ((left >> __lane_id()) & 1ull) rank = atomicAdd(count + tile, 1u);
+            uint32_t rank = 0;
+            if (lead == self) rank = atomicAdd(count + tile, together);
+            rank = (uint32_t)__shfl((int)rank, lead, 64) + before;
             tile_rank[k] = rank;
         }
     }
@@ -507,11 +510,11 @@ __global__ __launch_bounds__(256) void place_kernel(const uint32_t* tile_keys, c
 // done in turn.  Up to kRunsFrom entries the workgroup reads the whole list; of a list beyond, tile_runs_kernel has
 // sorted runs, and it searches each of them for the ends of its range.  Reading grows with the square of the list,
 // but up to the line it takes about as long as the radix sorts, and a launch without longer lists is not
-// delayed by the runs' kernel (2 us).  All binning, all Gaussians of a view in one tile, us:
+// delayed by the runs' kernel (4.5 us).  All binning, all Gaussians of a view in one tile, us:
 //   Gaussians                     5k   20k   50k  100k  200k  300k  400k  500k     1M
 //   one workgroup a list         197   954        6136
-//   reading the list              67    76    92   124   171   260   360   670
-//   searching runs               106    91    90    98   123   168   189   228    686
+//   reading the list              67    73    92   121   171   248   360   670
+//   searching runs               106    91    90    98   123   168   184   222    690
 //   radix sorts over all         115   120   151   215   220   222   228   232    266
 constexpr int kTileSortThreads = 256;
 constexpr int kTileSortItems = kTileSortMost / kTileSortThreads;
@@ -540,6 +543,7 @@ __device__ __forceinline__ void wave_sync() {
 // One level of merges of runs of R (a power of two) of n elements: element i to place(i's new place).
 template <typename Load, typename Place>
 __device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, Place place) {
+#pragma unroll 1
     for (uint32_t i0 = thread_number(); i0 < n; i0 += kMergeItems * kTileSortThreads) {
         unsigned long long key[kMergeItems];
         uint32_t lo[kMergeItems], ps[kMergeItems], pl[kMergeItems];  // the other run: start, length
@@ -552,6 +556,7 @@ __device__ __forceinline__ void merge_level(uint32_t n, uint32_t R, Load load, P
             pl[k] = in && ps[k] < n ? (n - ps[k] < R ? n - ps[k] : R) : 0u;
             lo[k] = 0;
         }
+#pragma unroll 1
         for (uint32_t step = R; step > 0; step >>= 1) {
 #pragma unroll
             for (int k = 0; k < kMergeItems; ++k) {
@@ -656,6 +661,7 @@ __device__ __forceinline__ bool bucket_sort(Id id_of, const uint32_t* pair_z, in
         at[k] = 0u;
     }
     __syncthreads();
+#pragma unroll 1
     for (uint32_t j = 0; j < most; ++j)
 #pragma unroll
         for (int k = 0; k < kTileSortItems; ++k)
@@ -701,6 +707,7 @@ __device__ __forceinline__ uint32_t merge_sort(Id id_of, const uint32_t* pair_z,
             run[lane] = key;
             wave_sync();
             rank = 0;
+#pragma unroll 4
             for (int j = 0; j < 64; ++j) rank += run[j] < key ? 1 : 0;
             wave_sync();
             run[rank] = key;
@@ -708,6 +715,7 @@ __device__ __forceinline__ uint32_t merge_sort(Id id_of, const uint32_t* pair_z,
     }
     __syncthreads();
     uint32_t from = 0;
+#pragma unroll 1
     for (uint32_t R = 64; R < len; R <<= 1, from ^= kTileSortMerge) {
         const u64* const in = buf + from;
         u64* const out = buf + (from ^ kTileSortMerge);
@@ -769,8 +777,9 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_runs_kernel(const uint3
 // Workgroups 0 .. n_work - 1: the lists of up to kTileSortMost entries, in the raster work order, the longest
 // first; the others, last because most launches have none of them: the segments in segs (their number in
 // segs[0].x, then (tile, segment)).  A tile's ids in `list` go to qb in order, the tile's id to tiles; runs: null
-// where no list can be longer than kRunsFrom.  Seven waves a SIMD by the LDS: the registers are held to those,
-// which costs the segments a spill (of 96 registers; without, all lists of a 300k view take 4 us longer).
+// where no list can be longer than kRunsFrom.  The LDS lets seven waves a SIMD run, and the registers have to: with 96
+// all lists of a 300k view took 4 us longer, with a spill the launch itself started 1.5 us later.  Hence the loops of the
+// segments are not unrolled, and a thread's number is formed anew in each of their parts.
 __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
     const uint32_t* pair_z, const uint32_t* ranges, const uint32_t* work, const uint2* segs, uint32_t n_work,
     const uint32_t* list, const uint32_t* runs, uint32_t* tiles, uint32_t* qb) {
@@ -808,13 +817,14 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
     uint32_t limit = segment ? kTileSortMost : kTileSortMerge;
     bool sampled = !segment;
     for (;;) {
-        const int t = thread_number();
         __syncthreads();
         uint32_t c = limit, below = 0u;
         if (!sampled) {
-            for (uint32_t i = t; i < c; i += kTileSortThreads) picked[i] = q[(uint32_t)((u64)i * n / c)];
+#pragma unroll 1
+            for (uint32_t i = thread_number(); i < c; i += kTileSortThreads) picked[i] = q[(uint32_t)((u64)i * n / c)];
             __syncthreads();
         } else {
+            const int t = thread_number();
             if (t == 0) n_in = 0u;
             __syncthreads();
             u64 least = ~0ull, most = 0ull;
@@ -822,6 +832,7 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
                 // each run's entries of [lo, hi) lie together: two binary searches a run, side by side
                 const uint32_t* const r = runs + s;
                 const uint32_t n_runs = (n + kTileSortMerge - 1) / kTileSortMerge;
+#pragma unroll 1
                 for (uint32_t i0 = t; i0 < n_runs; i0 += kMergeItems * kTileSortThreads) {
                     uint32_t from[kMergeItems], first_in[kMergeItems], first_out[kMergeItems], len[kMergeItems];
 #pragma unroll
@@ -831,6 +842,7 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
                         len[k] = i < n_runs ? (n - from[k] < kTileSortMerge ? n - from[k] : kTileSortMerge) : 0u;
                         first_in[k] = first_out[k] = 0u;
                     }
+#pragma unroll 1
                     for (uint32_t step = kTileSortMerge; step > 0; step >>= 1) {
 #pragma unroll
                         for (int k = 0; k < kMergeItems; ++k) {
@@ -847,6 +859,7 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
                         least = x < least ? x : least;
                         most = y > most ? y : most;
                         const uint32_t k_in = first_out[k] - first_in[k], p = atomicAdd(&n_in, k_in);
+#pragma unroll 1
                         for (uint32_t e = 0; e < k_in && p + e < limit; ++e)
                             picked[p + e] = r[from[k] + first_in[k] + e];
                     }
@@ -864,6 +877,7 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
                     }
                 };
                 load(t);
+#pragma unroll 1
                 for (uint32_t i0 = t; i0 - t < n; i0 += U * kTileSortThreads) {
                     uint32_t z[U], now[U];
 #pragma unroll
@@ -917,7 +931,8 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
             sampled = true;
             continue;
         }
-        for (uint32_t i = t; i < c; i += kTileSortThreads) {
+#pragma unroll 1
+        for (uint32_t i = thread_number(); i < c; i += kTileSortThreads) {
             tiles[s + below + i] = tile;
             qb[s + below + i] = (uint32_t)buf[from + i];
         }
@@ -960,7 +975,7 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
 // over 1M (7.5M) 304 and 361.  Long lists cost it the most (see the table at bucket_sort): lists are at most 4096
 // entries long because no view has more Gaussians, or the capacity leaves 512 a tile on average, which bounds
 // no single list, and no view has more than 2^20 Gaussians.  If those all lie in one tile it is as fast as the radix
-// sorts up to 500k, at 1M 686 us and 266.  Its scans, of 2048 pairs or 1024 tiles a workgroup, each of which adds up the
+// sorts up to 500k, at 1M 690 us and 266.  Its scans, of 2048 pairs or 1024 tiles a workgroup, each of which adds up the
 // sums of those before it, grow with the square of their number: per tile and by radix sorts, 30k Gaussians in
 // 32,400 tiles 109 and 124 us, 65,536 tiles 151 and 143, 129,600 tiles 233 and 161 (200k: 138 and 222, 213 and 240, 369
 // and 251); 4.2M pairs of which 400k are visible 234 and 252, 8.4M 395 and 371, 34M 1514 and 1099.
