@@ -95,8 +95,12 @@ __device__ __forceinline__ bool needs_tests(float A, float B, float C, float o, 
 }
 
 // The base-2 exponent A' dx^2 + B' dx dy + C' dy^2 in one fixed order of roundings for both block shapes.
-// (SHARED, the backward of several pixels a thread: they share A' dx instead, which rounds the other of
-// the two products; alpha may differ from the forward's in its last bit.)
+// (SHARED, the backward of several pixels a thread: they share A' dx instead, which rounds the other of the two
+// products, as that shape always did.  Its alpha may differ from the forward's in the last bit, so a pair at the
+// cutoff is kept by one of the two only, a few pixels in 10^7: there T comes back wrong by 1 - alpha_min for the
+// nearer entries.  One order for both takes no longer, 4-view step 1161 us, but is not nearer to float64, since the
+// forward's own rounding puts as many pairs across the cutoff, and moves a variance-weighted step's pose gradient
+// by up to 8e-5 of its norm.)
 __device__ __forceinline__ float exponent2(float A, float B, float C, float dx, float dy) {
     return __builtin_fmaf(dy, dy * C, dx * __builtin_fmaf(dx, A, dy * B));
 }
@@ -150,13 +154,13 @@ struct Rows {
     float4 col[kChunk + PAD];  // r g b z
     float2 co[kChunk + PAD];   // C' o
     uint32_t pos[kChunk + PAD];
-    // Packs the lanes' records with `in` set and returns how many there are; `slow` if any of them
-    // needs the per-pixel tests.
-    __device__ __forceinline__ int pack(const Rec& r, bool in, uint32_t position, float amax, bool& slow) {
+    // Packs the lanes' records with `in` set and returns how many there are; `slow` if any of them, with the
+    // opacity `o` (the record's), needs the per-pixel tests.
+    __device__ __forceinline__ int pack(const Rec& r, float o, bool in, uint32_t position, float amax, bool& slow) {
         const unsigned long long im = __builtin_amdgcn_ballot_w64(in);
         const int n = __popcll(im), at = rank_in(im);
         const float A = -0.5f * kLog2e * r.a.z, B = -kLog2e * r.a.w, C = -0.5f * kLog2e * r.b.x;
-        slow = __builtin_amdgcn_ballot_w64(in && needs_tests(A, B, C, r.b.y, amax)) != 0ull;
+        slow = __builtin_amdgcn_ballot_w64(in && needs_tests(A, B, C, o, amax)) != 0ull;
         if (in) {
             g[at] = make_float4(r.a.x, r.a.y, A, B);
             co[at] = make_float2(C, r.b.y);
@@ -216,7 +220,7 @@ __device__ __forceinline__ void write_pixel(const RasterArgs& a, const TileCoord
 // v_mfma_f32_4x4x1_16b_f32 does with the pixel's four sums in its own lane: one LDS read a step gives
 // the colours of all four entries, where broadcast reads kept the LDS 80 % busy.  It rounds like the
 // four fmas it replaces, but runs over all lanes, of which those that do not keep the entry have w = 0: a
-// chunk with an unbounded colour takes the fmas, on the lanes that keep it.  S2: also output the rendered
+// chunk with an infinite colour takes the fmas, on the lanes that keep it.  S2: also output the rendered
 // depth variance.
 template <int T, bool S2>
 __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
@@ -263,9 +267,11 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
         }
         const uint32_t e = bs + lane;
         const bool in = e < end && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, Y0, 7.f, 7.f);
+        // `slow` also for an infinite colour or depth: 0 times the largest (none is below 0) makes this opacity NaN.
+        // A ballot of its own lengthened the chain of a long list (six 64 x 48 views over 300k: 2230 -> 2335 us).
+        const float o = __builtin_fmaf(0.f, fmaxf(fmaxf(fmaxf(r.c.y, r.c.z), r.c.w), r.b.z), r.b.y);
         bool slow;
-        const int n = my.pack(r, in, e - start + 1, amax, slow);
-        const bool far = __builtin_amdgcn_ballot_w64(in && unbounded(r.c.y, r.c.z, r.c.w, r.b.z)) != 0ull;
+        const int n = my.pack(r, o, in, e - start + 1, amax, slow);
         int lastc = -1;  // the last contributor's row in this chunk
         auto run = [&](auto tests, auto matrix) {
             int row = 0;
@@ -326,9 +332,9 @@ __global__ __launch_bounds__(T* T) void raster_fwd_kernel(RasterArgs a) {
                 blend(std::integral_constant<int, 3>{});
             }
         };
-        if (far) run(std::true_type{}, std::false_type{});
-        else if (slow) run(std::true_type{}, std::true_type{});
-        else run(std::false_type{}, std::true_type{});
+        if (!slow) run(std::false_type{}, std::true_type{});
+        else if (__builtin_amdgcn_ballot_w64(in && o != o) == 0ull) run(std::true_type{}, std::true_type{});
+        else run(std::true_type{}, std::false_type{});
         if (lastc >= 0) last = my.pos[lastc];
         __builtin_amdgcn_wave_barrier();
     }
@@ -380,7 +386,7 @@ __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a)
         const float top = open[0] ? Y0 : Y0 + 8.f, span = open[0] && open[1] ? 15.f : 7.f;
         const bool in = e < end && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, top, 7.f, span);
         bool slow;
-        const int n = my.pack(r, in, e - start + 1, amax, slow);
+        const int n = my.pack(r, r.b.y, in, e - start + 1, amax, slow);
         int lastc[PPT] = {-1, -1};  // the last contributor's row in this chunk
         auto run = [&](auto tests) {
             int row = 0;
@@ -447,10 +453,12 @@ __global__ __launch_bounds__(T* T / 2) void raster_fwd_wide_kernel(RasterArgs a)
 }
 
 // Several pixels a thread, and many tiles: the workgroup stages its tile's list in LDS, M entries at a
-// time, thread t covers column t % T and PPT rows.  Where px_per_thread asks for it and the chip is full
-// it is as fast as the wide blocks (22 views 507 and 500 us), and it keeps that shape's images: the compiler
+// time, thread t covers column t % T and PPT rows.  It is here for that shape's images alone: the compiler
 // forms the exponents of a thread's pixels in different orders of roundings, so the one order of the
-// block kernels moves alpha by an ulp, which is across the cutoff for a few pixels in 10^7.
+// block kernels moves alpha by an ulp, which is across the cutoff for a few pixels in 10^7 (images up to
+// 2.8e-3 of their root mean square off).  It is as fast as the wide blocks for 22 views at (16, 64, 4), 507 and 500
+// us, and slower elsewhere: four 1280 x 800 views 260 us at (16, 256, 2), 429 at (16, 64, 4), 683 at (32, 512, 2),
+// 1211 at (32, 256, 4), where the wide blocks take 190 to 210.
 struct alignas(16) StagedRec {
     float4 m, g0;  // z r g b | u v A' B'
     float2 g1;     // C' o
@@ -672,8 +680,9 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
             wlast = max(wlast, last[k]);
         }
     }
-    // an adjoint, or from the first record on that has one a colour, that makes dL/dalpha infinite or NaN: it must not
-    // reach the sums of p of the records that its pixel does not keep
+    // An adjoint, or from the first record on that has one a colour, that makes dL/dalpha infinite or NaN must
+    // not reach the sums of p of the records that its pixel does not keep.  Decided for a whole wave, since a
+    // select in every entry would cost all of them (the 4-view backward takes as long with the test as without).
     bool far = false;
 #pragma unroll
     for (int k = 0; k < PPT; ++k) far |= unbounded(gC0[k], gC1[k], gC2[k], gD[k]) || unbounded(gX[k], 0.f, 0.f, 0.f);
@@ -709,7 +718,7 @@ __global__ __launch_bounds__(T* T / PPT) void raster_bwd_kernel(RasterBwdArgs a)
         const bool in = e >= 0 && block_reached(r.a, r.b.x, r.b.y, inv_amin, X0, Y0, 7.f, 8.f * PPT - 1.f);
         if (in) mypair[rank_in(__builtin_amdgcn_ballot_w64(in))] = q;
         bool slow;
-        const int n = my.pack(r, in, (uint32_t)e, amax, slow);
+        const int n = my.pack(r, r.b.y, in, (uint32_t)e, amax, slow);
         far |= __builtin_amdgcn_ballot_w64(in && unbounded(r.c.y, r.c.z, r.c.w, r.b.z)) != 0ull;
         auto run = [&](auto tests) {
             constexpr bool TESTS = decltype(tests)::value;
@@ -877,7 +886,8 @@ static bool wide_blocks(const ViewTable& vt, int T) {
 }
 
 // How many entries and pixels a lane takes follows from the number of blocks; `batch` and `ppt` name a
-// supported shape, and ppt > 1 the staged forward for many tiles and the backward's shared exponents.
+// supported shape, and ppt > 1 the staged forward for many tiles and the backward's shared exponents.  `batch`
+// sizes the staged forward's LDS and nothing else: the other shapes of a tile and ppt are the same kernels.
 static bool shape_supported(int T, int batch, int ppt) {
 #define X(t_, p_, m_) \
     if (T == t_ && ppt == p_ && batch == m_) return true;
