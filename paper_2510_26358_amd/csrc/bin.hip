@@ -777,9 +777,9 @@ __global__ __launch_bounds__(kTileSortThreads) void tile_runs_kernel(const uint3
 // Workgroups 0 .. n_work - 1: the lists of up to kTileSortMost entries, in the raster work order, the longest
 // first; the others, last because most launches have none of them: the segments in segs (their number in
 // segs[0].x, then (tile, segment)).  A tile's ids in `list` go to qb in order, the tile's id to tiles; runs: null
-// where no list can be longer than kRunsFrom.  The LDS lets seven waves a SIMD run, and the registers have to: with 96
-// all lists of a 300k view took 4 us longer, with a spill the launch itself started 1.5 us later.  Hence the loops of the
-// segments are not unrolled, and a thread's number is formed anew in each of their parts.
+// where no list can be longer than kRunsFrom.  The LDS lets seven waves a SIMD run, and the registers have to:
+// with 96 all lists of a 300k view took 4 us longer, with a spill the launch itself started 1.5 us later.
+// Hence the loops of the segments are not unrolled, and a thread's number is formed anew in each of their parts.
 __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
     const uint32_t* pair_z, const uint32_t* ranges, const uint32_t* work, const uint2* segs, uint32_t n_work,
     const uint32_t* list, const uint32_t* runs, uint32_t* tiles, uint32_t* qb) {
@@ -821,7 +821,8 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
         uint32_t c = limit, below = 0u;
         if (!sampled) {
 #pragma unroll 1
-            for (uint32_t i = thread_number(); i < c; i += kTileSortThreads) picked[i] = q[(uint32_t)((u64)i * n / c)];
+            for (uint32_t i = thread_number(); i < c; i += kTileSortThreads)
+                picked[i] = q[(uint32_t)((u64)i * n / c)];
             __syncthreads();
         } else {
             const int t = thread_number();
@@ -908,7 +909,8 @@ __global__ __launch_bounds__(kTileSortThreads, 7) void tile_sort_kernel(
             most = uniform64(most);
             below = uniform32(below);
             c = uniform32(n_in);
-            if (c > limit) {  // of at least two distinct keys
+            if (c > limit) {
+                if (least == most) return;  // a tile lists a pair once, so keys are distinct: buffers in use twice
                 hi = least + (most - least) / 2 + 1;
                 continue;
             }
@@ -974,11 +976,12 @@ void launch_count_from_records(const ViewTable& vt, const float* records, const 
 // intersections) 190 us by radix sorts, 51 tile by tile; three views over 600k (2.4M) 208 and 158; four
 // over 1M (7.5M) 304 and 361.  Long lists cost it the most (see the table at bucket_sort): lists are at most 4096
 // entries long because no view has more Gaussians, or the capacity leaves 512 a tile on average, which bounds
-// no single list, and no view has more than 2^20 Gaussians.  If those all lie in one tile it is as fast as the radix
-// sorts up to 500k, at 1M 690 us and 266.  Its scans, of 2048 pairs or 1024 tiles a workgroup, each of which adds up the
-// sums of those before it, grow with the square of their number: per tile and by radix sorts, 30k Gaussians in
-// 32,400 tiles 109 and 124 us, 65,536 tiles 151 and 143, 129,600 tiles 233 and 161 (200k: 138 and 222, 213 and 240, 369
-// and 251); 4.2M pairs of which 400k are visible 234 and 252, 8.4M 395 and 371, 34M 1514 and 1099.
+// no single list, and no view has more than 2^20 Gaussians.  If those all lie in one tile it is as fast as the
+// radix sorts up to 500k, at 1M 690 us and 266.  Its scans, of 2048 pairs or 1024 tiles a workgroup, each of
+// which adds up the sums of those before it, grow with the square of their number: per tile and by radix sorts,
+// 30k Gaussians in 32,400 tiles 109 and 124 us, 65,536 tiles 151 and 143, 129,600 tiles 233 and 161 (200k: 138 and
+// 222, 213 and 240, 369 and 251); 4.2M pairs of which 400k are visible 234 and 252, 8.4M 395 and 371, 34M
+// 1514 and 1099.
 constexpr long long kTileSortCapacity = 1ll << 22, kTileSortShort = 4096, kTileSortMean = 512;
 constexpr long long kTileSortLongest = 1ll << 20, kTileSortTiles = 1ll << 16, kTileSortPairs = 1ll << 23;
 // No list is longer than its view's Gaussian range, or than the capacity.
@@ -996,8 +999,8 @@ static bool per_tile_sort(const ViewTable& vt, long long n_pairs, long long capa
     return longest <= kTileSortShort || (longest <= kTileSortLongest && capacity <= kTileSortMean * n_tiles);
 }
 
-// Two sets of counts, then the segments.  Reserved for every launch, whichever way it takes: the workspace of a larger
-// capacity, view or map has room for a smaller one.
+// Two sets of counts, then the segments.  Reserved for every launch, whichever way it takes: the workspace of a
+// larger capacity, view or map has room for a smaller one.
 size_t tile_sort_bytes(long long n_tiles, long long capacity) {
     const size_t tiles = (size_t)min(n_tiles, kTileSortTiles), cap = (size_t)min(capacity, kTileSortCapacity);
     return 2 * kTileCounts * tiles * sizeof(uint32_t) + (1 + (size_t)tile_sort_segments(cap)) * sizeof(uint2);
