@@ -325,16 +325,17 @@ int ags_pose_step(ags_ctx* ctx, const ags_adam* hp, ags_camera* cams, int32_t n_
 
 /* Autotuner for the raster launch shapes (tiling is "standard 3DGS" in Sec. III-B; the paper
  * names no tile size or batch).  For every tile size in {8, 16, 32} and every (LDS batch,
- * pixels per thread) shape compiled for it (the list under ags_config), times `steps`
+ * pixels per thread) shape supported for it (the list under ags_config), times `steps`
  * forward + fused-loss backward steps of this workload (views, g, cams, loss as for
  * ags_render_fwd / ags_render_bwd), after `warmup` untimed ones, on `stream` with HIP events
- * per stage.  Per tile size it takes the forward shape with the fastest raster forward and
+ * per stage (shapes that run the same kernels over these views are timed once, and the first of
+ * them is the one that is picked).  Per tile size it takes the forward shape with the fastest raster forward and
  * the backward shape with the fastest raster backward, predicts the step as the rest of the
  * first shape's step plus those two, and picks the tile size with the fastest prediction.
  * The pick (other fields from the context's configuration) is written to *best and set on
  * the context; *predicted_step_ms (nullable) receives its predicted step time.  report
  * (nullable unless n_report_max > 0) receives up to n_report_max per-shape timings and
- * *n_report (nullable) the number of shapes timed.  Off the hot path: it allocates its trial
+ * *n_report (nullable) the number of shapes.  Off the hot path: it allocates its trial
  * buffers (device memory for outputs, gradients and the saved state at each tile size's
  * intersection capacity, freed before it returns) and synchronises with the host; g is only
  * read.  The caller's profile totals are kept.  Errors: INVALID_ARG, CAPACITY (more than

@@ -1100,11 +1100,22 @@ int ags_tune(ags_ctx* ctx, const ags_views* views, const ags_gaussians* g, const
         Layout L;
         rc = build_layout(&ctx->cfg, views, g->n, cap, L);
         if (rc) break;
-        double t_first = 0.0, f_first = 0.0, b_first = 0.0;
-        double best_f = 1e300, best_b = 1e300;
-        int bf = first, bb = first;
+        // shapes of the same two kernels are timed once, and each kernel is picked by its first shape: one timing
+        // differs from the next by more than nothing
+        double step_ms[32], f_ms[32], b_ms[32];
+        int f_id[32], b_id[32];
         for (int k = 0; k < n_shapes && rc == AGS_OK; ++k) {
             if (sh_tile[k] != T) continue;
+            f_id[k] = raster_kernel_of(L.vt, T, sh_batch[k], sh_ppt[k], false);
+            b_id[k] = raster_kernel_of(L.vt, T, sh_batch[k], sh_ppt[k], true);
+            int like = first;
+            while (like < k && (sh_tile[like] != T || f_id[like] != f_id[k] || b_id[like] != b_id[k])) ++like;
+            if (like < k) {
+                step_ms[k] = step_ms[like];
+                f_ms[k] = f_ms[like];
+                b_ms[k] = b_ms[like];
+                continue;
+            }
             ctx->cfg.batch = sh_batch[k];
             ctx->cfg.px_per_thread = sh_ppt[k];
             ctx->cfg.batch_bwd = ctx->cfg.px_per_thread_bwd = 0;
@@ -1135,37 +1146,38 @@ int ags_tune(ags_ctx* ctx, const ags_views* views, const ags_gaussians* g, const
             if (rc) break;
             float wall = 0.f;
             (void)hipEventElapsedTime(&wall, e0, e1);
-            const double step_ms = wall / steps;
-            const double f_ms = ctx->total_ms[ST_RASTER_FWD] / steps;
-            const double b_ms = ctx->total_ms[ST_RASTER_BWD] / steps;
+            step_ms[k] = wall / steps;
+            f_ms[k] = ctx->total_ms[ST_RASTER_FWD] / steps;
+            b_ms[k] = ctx->total_ms[ST_RASTER_BWD] / steps;
+        }
+        if (rc) break;
+        auto fastest = [&](const double* ms, const int* id, double& least) {
+            int at = first;
+            for (int k = first; k < n_shapes; ++k)
+                if (sh_tile[k] == T && ms[k] < ms[at]) at = k;
+            least = ms[at];
+            for (int k = first; k < at; ++k)
+                if (sh_tile[k] == T && id[k] == id[at]) return k;
+            return at;
+        };
+        double best_f = 0.0, best_b = 0.0;
+        const int bf = fastest(f_ms, f_id, best_f), bb = fastest(b_ms, b_id, best_b);
+        for (int k = first; k < n_shapes; ++k) {
+            if (sh_tile[k] != T) continue;
             if (n_rep < n_report_max) {
                 ags_tune_entry& e = report[n_rep];
                 e.tile = T;
                 e.batch = sh_batch[k];
                 e.px_per_thread = sh_ppt[k];
-                e.step_ms = (float)step_ms;
-                e.raster_fwd_ms = (float)f_ms;
-                e.raster_bwd_ms = (float)b_ms;
+                e.step_ms = (float)step_ms[k];
+                e.raster_fwd_ms = (float)f_ms[k];
+                e.raster_bwd_ms = (float)b_ms[k];
                 e.intersections = K;
             }
             ++n_rep;
-            if (k == first) {
-                t_first = step_ms;
-                f_first = f_ms;
-                b_first = b_ms;
-            }
-            if (f_ms < best_f) {
-                best_f = f_ms;
-                bf = k;
-            }
-            if (b_ms < best_b) {
-                best_b = b_ms;
-                bb = k;
-            }
         }
-        if (rc) break;
         // the rest of the first shape's step, plus the fastest forward and backward shapes
-        const double total = (t_first - f_first - b_first) + best_f + best_b;
+        const double total = (step_ms[first] - f_ms[first] - b_ms[first]) + best_f + best_b;
         if (total < pick_total) {
             pick_total = total;
             pick = base;

@@ -12,8 +12,8 @@ constexpr int kMaxViews = AGS_MAX_VIEWS;
 constexpr int kRecFloats = 12;       // projected record: u v a b c o z ex ey r g b
 // per-pair 2D adjoint: 5 pixel moments of p = dL/dpower (turned into the centre and conic
 // adjoints by the projection backward), the sum of p (o dL/do), then r, g, b, z.  The kGrad2dSplit
-// sums of p, whose terms cancel, are kept in two parts (slots 0..5 and 10..15) that different waves
-// add to: half as long a chain of float additions into each.
+// sums of p, whose terms cancel, are kept in two parts (slots 0..5 and 10..15) that a tile's even and odd waves
+// add to: half as long a chain of float additions into each.  (An 8-pixel tile has one wave, and one part.)
 constexpr int kGrad2d = 10;
 constexpr int kGrad2dSplit = 6;
 constexpr int kGrad2dStride = 16;  // 64-byte rows: a row is one cache line
@@ -529,6 +529,8 @@ struct RasterArgs {
 // returns how many there are.
 int raster_shapes(int* tile, int* ppt, int* batch, int n_max);
 int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_t s);
+// A number that two shapes of one tile edge share if they run the same kernel over these views.
+int raster_kernel_of(const ViewTable& vt, int T, int batch, int ppt, bool backward);
 
 struct RasterBwdArgs {
     ViewTable vt;

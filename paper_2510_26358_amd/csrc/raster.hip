@@ -896,6 +896,11 @@ static bool shape_supported(int T, int batch, int ppt) {
     return false;
 }
 
+int raster_kernel_of(const ViewTable& vt, int T, int batch, int ppt, bool backward) {
+    if (backward) return T == 16 && ppt > 1 ? 1 : 0;
+    return wide_blocks(vt, T) && ppt > 1 ? 1024 * ppt + batch : 0;
+}
+
 int launch_raster_fwd(const RasterArgs& a, int T, int batch, int ppt, hipStream_t s) {
     const int nb = raster_blocks(a.vt);
     if (nb <= 0) return 0;

@@ -58,8 +58,7 @@ long long ssim_blocks(const ViewTable& vt) {
     return 3 * t;
 }
 
-// Odd row strides, so that lanes of consecutive rows touch different banks.  50 KB: three workgroups
-// share a CU.
+// Odd row strides, so that lanes of consecutive rows touch different banks.  26 KB.
 union SsimShared {
     float v[2][kSsimMH][kSsimIW + 1];  // two of the column-blurred x, y, x^2 + y^2, x y
     float d[3][kSsimMH][kSsimMW + 1];

@@ -1,8 +1,12 @@
 """Autotuner front end for the raster launch shapes: tile edge T (shared by binning, forward
-and backward), and for each raster kernel its Gaussians per LDS batch and pixels per thread.
+and backward), and for each raster kernel its batch and pixels per thread.
+
+Several pixels per thread select the forward that stages whole tiles, `batch` Gaussians at a
+time, where a launch has many tiles, and the order of roundings of the backward's exponents;
+otherwise shapes of one tile edge run the same kernels and are timed once.
 
 The search runs in the library (`ags_tune`): for every tile size and every launch shape
-compiled for it, a few full forward + backward steps of the caller's workload are timed with
+of it, a few full forward + backward steps of the caller's workload are timed with
 per-stage HIP events; the forward and backward shapes are chosen independently (they only
 share T) and the tile size with the smallest resulting step time wins.  This module keeps
 the host policy: picks are cached in a JSON file keyed by device name and workload shape,
