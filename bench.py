@@ -37,9 +37,9 @@ TRIALS = 5  # timing: median over this many trials of `steps` replays each
 # backward ~60 + 1 exp; the exp is counted as one FLOP.
 FLOP_PER_PAIR = {"raster_fwd": 21, "raster_bwd": 61}
 # Algorithmic FLOP of the D-SSIM term per pixel and colour channel (no halo recomputation):
-# five window moments by two 11-tap passes (220), s and its three partial derivatives (~40),
-# three 11-tap passes back (132), the final combination (~8).
-SSIM_FLOP_PER_PIXEL_CHANNEL = 400
+# four window moments by two 11-tap passes (176; the variances enter through their sum alone), s and
+# its three partial derivatives (~40), three maps back by two 11-tap passes (132), the final combination (~8).
+SSIM_FLOP_PER_PIXEL_CHANNEL = 356
 PROFILES = os.path.join(ROOT, "profiles")
 
 
